@@ -159,14 +159,27 @@ __device__ __forceinline__ void hvp_apply(const ElemOut<Term, T>& o, T te, const
     }
 }
 
-// hardware reciprocal / square root / reciprocal square root: approximate (about 1 ulp) in FP32,
-// IEEE in FP64
+// Reciprocal and reciprocal square root: the hardware's in FP32 (about 1 ulp); in FP64 the hardware's
+// estimate and Newton steps, within a few ulps, at a quarter of the instructions of the IEEE division and
+// square root.
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double frcp(double x) { return 1.0 / x; }
-__device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double fsqrt(double x) { return sqrt(x); }
+__device__ __forceinline__ double frcp(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
 __device__ __forceinline__ float frsq(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double frsq(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ double frsq(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    const double e = fma(-x * y, y, 1.0);   // one Newton step more, to third order
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+// sqrt(x) for x no smaller than the least normal number
+__device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ __forceinline__ double fsqrt(double x) { return x * frsq(x); }
+__device__ __forceinline__ float least_normal(float) { return 1.17549435e-38f; }
+__device__ __forceinline__ double least_normal(double) { return 2.2250738585072014e-308; }
 
 // ---- symmetric eigen-decomposition: Jacobi rotations in round-robin order --------------------
 // A sweep visits every pair (p, q) once, grouped into rounds of disjoint pairs (circle method
@@ -175,8 +188,8 @@ __device__ __forceinline__ double frsq(double x) { return 1.0 / sqrt(x); }
 // problems on multiprocessor arrays" (SIAM J. Sci. Stat. Comput., 1985). Rotations
 // in one round touch disjoint (p, q) planes, so their parameters depend only on entries no other
 // rotation of the round changes: they are computed together, giving independent instruction
-// streams. The rotation zeroing a_pq uses t = tan(phi) = sgn(d) 2 a_pq / (|d| + sqrt(d^2 + 4 a_pq^2)),
-// d = a_qq - a_pp (the smaller root of t^2 + 2 t d / (2 a_pq) - 1 = 0), c = 1/sqrt(1 + t^2),
+// streams. The rotation zeroing a_pq uses t = tan(phi) = a_pq / (h + sgn(h) sqrt(h^2 + a_pq^2)),
+// h = (a_qq - a_pp) / 2 (the smaller root of t^2 + 2 t h / a_pq - 1 = 0), c = 1/sqrt(1 + t^2),
 // s = t c, and A <- J^T A J, V <- V J with J_pp = J_qq = c, J_pq = s, J_qp = -s.
 //
 // Scaled rotations (the idea of the fast Givens transformation of W. M. Gentleman, 1973, and
@@ -226,11 +239,10 @@ __device__ __forceinline__ void jacobi_sweep(T (&A)[Packed<N>::N], T (&W)[N][N],
             if (a >= N || b >= N) continue;
             const int p = a < b ? a : b, q = a < b ? b : a;
             const T apq = dsc[p] * dsc[q] * A[Packed<N>::at(p, q)];
-            const T d = A[Packed<N>::at(q, q)] - A[Packed<N>::at(p, p)];
-            const T den = fabs(d) + fsqrt(d * d + T(4) * apq * apq);
-            T t = (T(2) * apq) * frcp(den);
-            t = d < T(0) ? -t : t;
-            t = (apq == T(0)) ? T(0) : t;
+            const T h = T(0.5) * A[Packed<N>::at(q, q)] - T(0.5) * A[Packed<N>::at(p, p)];
+            // the floor keeps t finite (and 0 for a_pq = 0) where h^2 + a_pq^2 underflows
+            const T root = fsqrt(fmax(h * h + apq * apq, least_normal(h)));
+            const T t = apq * frcp(h + copysign(root, h));
             tn[k] = t;
             ta[k] = t * apq;
         }
@@ -321,12 +333,291 @@ template <> struct JacobiTol<double> {
     static constexpr int sweeps = 25;
 };
 
+// What element_derivs leaves for element_clamp: the Hessian to clamp, in Helmert coordinates, Hq = (W (x) I)^T
+// H_r (W (x) I); for the terms with a frame (below) the part of it that the frame leaves, the frame's axes (the
+// columns of R) and, for a hinge, the unit vector of its null direction.
+template <class Term, typename T, int FRAME = Term::FRAME>
+struct ClampIn {
+    T A[Packed<Term::KR>::N];
+};
+template <class Term, typename T>
+struct ClampIn<Term, T, 1> {
+    T A[Packed<8>::N], R[3][3], v[3];
+};
+template <class Term, typename T>
+struct ClampIn<Term, T, 2> {
+    T A[Packed<4>::N], B[3], R[3][3];
+};
+
+// ---- clamp in a frame of the element ----------------------------------------------------------
+// Turning the element turns its Hessian, so the derivatives can be taken in orthonormal axes (u, m, n) of the
+// current element, where most coordinates vanish (the compiler folds the products with them) and part of the
+// Hessian is known to be zero. The eigen-decomposition of the remaining part gives the same clamped matrix.
+//
+// Membrane (FRAME 2: an energy of the triangle's metric r_i . r_j): u along r_1, m in its plane, n its normal.
+// The second derivative of r_i . r_j couples equal axes only and its first derivative has no n part, so the
+// 6 x 6 Hessian falls into a 4 x 4 in-plane matrix and a 2 x 2 matrix along n: 6 + 1 rotations of 12 and 4
+// multiply-adds a sweep instead of 15 of 20, and three sweeps instead of five.
+//
+// Hinge (FRAME 1: a function of the dihedral angle theta): u along the hinge e, (u, m) the first face. theta
+// does not change when any of e, a, b moves along u, which makes the u-u part of the Hessian zero; and the
+// stretch along u of the whole element also leaves the gradient as it is, so the Hessian annihilates that
+// direction v (x) u, v the unit vector of the Helmert u-coordinates. With the other two u directions in a
+// basis orthogonal to v an 8 x 8 matrix remains: 28 rotations of 28 multiply-adds a sweep instead of 36 of 32,
+// and four sweeps instead of five (over a wave of 64 elements of the benchmark shell, FP32 emulation).
+__device__ __forceinline__ double dot3(const double (&a)[3], const double (&b)[3]) {
+    return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+}
+__device__ __forceinline__ void cross3(const double (&a)[3], const double (&b)[3], double (&c)[3]) {
+    c[0] = a[1] * b[2] - a[2] * b[1];
+    c[1] = a[2] * b[0] - a[0] * b[2];
+    c[2] = a[0] * b[1] - a[1] * b[0];
+}
+// |e| to within a rounding from e.e and its reciprocal root
+__device__ __forceinline__ double length_of(double ee, double il) {
+    const double l = ee * il;
+    return fma(0.5 * il, fma(-l, l, ee), l);
+}
+// The unit normal n loses its orthogonality to u as the triangle degenerates: that part is taken out again.
+// m = n x u.
+template <typename T>
+__device__ __forceinline__ void finish_frame(const double (&u)[3], double (&m)[3], double (&n)[3]) {
+    const double nu = dot3(n, u);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) n[c] -= nu * u[c];
+    if constexpr (sizeof(T) == 8) {
+        const double in2 = frsq(dot3(n, n));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) n[c] *= in2;
+    }
+    cross3(n, u, m);
+}
+
+// entry (i, ax; j, bx) of the Helmert-coordinate Hessian from the packed one over the relative coordinates
+template <class Term, typename T>
+__device__ __forceinline__ T helmert_entry(const T (&h)[Packed<Term::KR>::N], int bi, int ci, int bj, int cj) {
+    constexpr int NS = Term::NS, D = Term::D, KR = Term::KR;
+    T acc = T(0);
+#pragma unroll
+    for (int a = 0; a < NS - 1; ++a) {
+        const double wa = wmat(a, bi);
+        if (wa == 0.0) continue;
+#pragma unroll
+        for (int b = 0; b < NS - 1; ++b) {
+            const double wb = wmat(b, bj);
+            if (wb == 0.0) continue;
+            acc += T(wa * wb) * h[Packed<KR>::at(a * D + ci, b * D + cj)];
+        }
+    }
+    return acc;
+}
+
+// Energy and stencil gradient: in FP32 from the derivatives g over the relative coordinates in the axes
+// (u, m, n); in FP64 from first-order duals in the caller's axes (a few per cent of the element's work), since
+// the gradients of neighbouring elements cancel and the rounding of the axes would show.
+template <class Term, typename T>
+__device__ __forceinline__ void frame_gradient(double f, const T (&g)[Term::KR], const double (&r)[Term::KR],
+                                               const double* rest, const double* prm, const T (&R)[3][3],
+                                               ElemOut<Term, T>& out) {
+    T gx[Term::KR];
+    if constexpr (sizeof(T) == 8) {
+        using S = D1<Term::KR, T>;
+        S rs[Term::KR];
+#pragma unroll
+        for (int i = 0; i < Term::KR; ++i) rs[i] = var<S>(i, r[i]);
+        const S q = Term::template energy<S>(rs, rest, prm);
+        out.f = q.v;
+#pragma unroll
+        for (int i = 0; i < Term::KR; ++i) gx[i] = q.g[i];
+    } else {
+        out.f = f;
+#pragma unroll
+        for (int s = 0; s < Term::KR; s += 3)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) gx[s + c] = R[c][0] * g[s] + R[c][1] * g[s + 1] + R[c][2] * g[s + 2];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        T g0 = T(0);
+#pragma unroll
+        for (int s = 1; s < Term::NS; ++s) {
+            out.g[s * 3 + c] = gx[(s - 1) * 3 + c];
+            g0 -= gx[(s - 1) * 3 + c];
+        }
+        out.g[c] = g0;
+    }
+}
+
+// hinge: position of (axis, Helmert index) in the 8 x 8 matrix: n 0-2, m 3-5, then the two u directions
+__host__ __device__ constexpr int hinge_n(int i) { return i; }
+__host__ __device__ constexpr int hinge_m(int i) { return 3 + i; }
+__host__ __device__ constexpr int hinge_u(int k) { return 6 + k; }
+
+// rows 1 and 2 of the reflection that takes the first unit vector to -sgn(v_0) v: an orthonormal basis of
+// the complement of v
+template <typename T>
+__device__ __forceinline__ void complement_rows(const T (&v)[3], T (&P)[2][3]) {
+    const T w0 = v[0] + copysign(T(1), v[0]), beta = frcp(T(1) + fabs(v[0]));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const T b = beta * v[1 + k];
+        P[k][0] = -b * w0;
+        P[k][1] = (k == 0 ? T(1) : T(0)) - b * v[1];
+        P[k][2] = (k == 1 ? T(1) : T(0)) - b * v[2];
+    }
+}
+
+template <class Term, typename T>
+__device__ __forceinline__ void hinge_derivs(const double (&r)[9], const double* rest, const double* prm,
+                                             ElemOut<Term, T>& out, ClampIn<Term, T, 1>& in) {
+    const double e[3] = {r[0], r[1], r[2]}, a[3] = {r[3], r[4], r[5]}, b[3] = {r[6], r[7], r[8]};
+    double u[3], m[3], n[3];
+    const double ee = dot3(e, e), il = frsq(ee), l = length_of(ee, il);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) u[c] = e[c] * il;
+    cross3(e, a, n);
+    const double inn = frsq(dot3(n, n));
+    // from the unrounded product: near a flat hinge theta is this small height over the first face's plane
+    const double bn = dot3(n, b) * inn;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) n[c] *= inn;
+    finish_frame<T>(u, m, n);
+    const double au = dot3(a, u), am = dot3(a, m), bu = dot3(b, u), bm = dot3(b, m);
+    using S = HD<9, T>;
+    const S rs[9] = {var<S>(0, l),  var<S>(1, 0.0), var<S>(2, 0.0), var<S>(3, au), var<S>(4, am),
+                     var<S>(5, 0.0), var<S>(6, bu),  var<S>(7, bm),  var<S>(8, bn)};
+    const S f = Term::template energy<S>(rs, rest, prm);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        in.R[c][0] = T(u[c]);
+        in.R[c][1] = T(m[c]);
+        in.R[c][2] = T(n[c]);
+    }
+    frame_gradient<Term, T>(f.v, f.g, r, rest, prm, in.R, out);
+    const double ru[3] = {l, au, bu};
+    T z[3], zz = T(0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        double q = 0.0;
+#pragma unroll
+        for (int s = 0; s < 3; ++s) q += helmert(s + 1, i) * ru[s];
+        z[i] = T(q * frsq(l * l + au * au + bu * bu));   // any scale: keeps the squares in range
+        zz += z[i] * z[i];
+    }
+    const T iz = frsq(zz);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) in.v[i] = z[i] * iz;
+    T P[2][3];
+    complement_rows<T>(in.v, P);
+    auto hq = [&](int i, int ci, int j, int cj) { return helmert_entry<Term, T>(f.h, i, ci, j, cj); };
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            if (j >= i) {
+                in.A[Packed<8>::at(hinge_n(i), hinge_n(j))] = hq(i, 2, j, 2);
+                in.A[Packed<8>::at(hinge_m(i), hinge_m(j))] = hq(i, 1, j, 1);
+            }
+            in.A[Packed<8>::at(hinge_n(i), hinge_m(j))] = hq(i, 2, j, 1);
+        }
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int ax = 1; ax < 3; ++ax) {
+            const T c0 = hq(0, 0, j, ax), c1 = hq(1, 0, j, ax), c2 = hq(2, 0, j, ax);
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                in.A[Packed<8>::at(ax == 2 ? hinge_n(j) : hinge_m(j), hinge_u(k))] =
+                    P[k][0] * c0 + P[k][1] * c1 + P[k][2] * c2;
+        }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int k2 = k; k2 < 2; ++k2) in.A[Packed<8>::at(hinge_u(k), hinge_u(k2))] = T(0);
+}
+
+template <class Term, typename T>
+__device__ __forceinline__ void membrane_derivs(const double (&r)[6], const double* rest, const double* prm,
+                                                ElemOut<Term, T>& out, ClampIn<Term, T, 2>& in) {
+    const double e[3] = {r[0], r[1], r[2]}, a[3] = {r[3], r[4], r[5]};
+    double u[3], m[3], n[3];
+    const double ee = dot3(e, e), aa = dot3(a, a), il = frsq(ee);
+    double l = length_of(ee, il);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) u[c] = e[c] * il;
+    cross3(u, a, n);
+    double nn = dot3(n, n);
+    if (ee <= 0.0 || nn <= 1e-28 * aa) {
+        // The energy is smooth at triangles without a plane, where any axes with u along their line serve: the
+        // longer of e and a and the coordinate axis furthest from it take the places of e and a.
+        double d[3], axis[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) d[c] = ee < aa ? a[c] : e[c];
+        const double x = fabs(d[0]), y = fabs(d[1]), z = fabs(d[2]), top = fmax(x, fmax(y, z));
+        const bool ax = x <= y && x <= z, ay = !ax && y <= z;
+        axis[0] = ax ? 1.0 : 0.0;
+        axis[1] = ay ? 1.0 : 0.0;
+        axis[2] = ax || ay ? 0.0 : 1.0;
+        if (top <= 0.0) d[1] = 1.0;   // all vertices in one point (the axis is then the first)
+        const double it = top > 0.0 ? 1.0 / top : 1.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) d[c] *= it;
+        const double id = frsq(dot3(d, d));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) u[c] = d[c] * id;
+        cross3(u, axis, n);
+        nn = dot3(n, n);
+        l = dot3(e, u);
+    }
+    const double inn = frsq(nn);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) n[c] *= inn;
+    finish_frame<T>(u, m, n);
+    using S = HD<6, T>;
+    const S rs[6] = {var<S>(0, l),          var<S>(1, 0.0),        var<S>(2, 0.0),
+                     var<S>(3, dot3(a, u)), var<S>(4, dot3(a, m)), var<S>(5, 0.0)};
+    const S f = Term::template energy<S>(rs, rest, prm);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        in.R[c][0] = T(u[c]);
+        in.R[c][1] = T(m[c]);
+        in.R[c][2] = T(n[c]);
+    }
+    frame_gradient<Term, T>(f.v, f.g, r, rest, prm, in.R, out);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = i; j < 4; ++j)
+            in.A[Packed<4>::at(i, j)] = helmert_entry<Term, T>(f.h, i >> 1, i & 1, j >> 1, j & 1);
+    in.B[0] = helmert_entry<Term, T>(f.h, 0, 2, 0, 2);
+    in.B[1] = helmert_entry<Term, T>(f.h, 0, 2, 1, 2);
+    in.B[2] = helmert_entry<Term, T>(f.h, 1, 2, 1, 2);
+}
+
+// blk (3 x 3 over the axes, the (i, j) block of a clamped matrix) turned back into the caller's axes
+template <class Term, typename T>
+__device__ __forceinline__ void rotate_block(const T (&B)[3][3], const T (&R)[3][3], int i, int j,
+                                             ElemOut<Term, T>& out) {
+    T t[3][3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) t[c][b] = R[c][0] * B[0][b] + R[c][1] * B[1][b] + R[c][2] * B[2][b];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            if (i == j && d < c) continue;
+            out.hr[Packed<Term::KR>::at(3 * i + c, 3 * j + d)] = t[c][0] * R[d][0] + t[c][1] * R[d][1] + t[c][2] * R[d][2];
+        }
+}
+
 // Derivatives of one element (modes 1-3): energy, stencil gradient, and the reduced Hessian --
-// for MODE 2 the raw Hessian in relative coordinates (into out.hr), for MODE 3 the Hessian in
-// Helmert coordinates Hq = (W (x) I)^T H_r (W (x) I) (into Aq, to be clamped by element_clamp).
+// for MODE 2 the raw Hessian in relative coordinates (into out.hr), for MODE 3 the matrix that
+// element_clamp takes (into in).
 template <class Term, typename T, int MODE>
 __device__ __forceinline__ void element_derivs(const double* xs, const double* rest, const double* prm,
-                                               ElemOut<Term, T>& out, T (&Aq)[Packed<Term::KR>::N]) {
+                                               ElemOut<Term, T>& out, ClampIn<Term, T>& in) {
     constexpr int NS = Term::NS, D = Term::D, KR = Term::KR;
     double r[KR];
     if constexpr (Term::TI) {
@@ -338,6 +629,13 @@ __device__ __forceinline__ void element_derivs(const double* xs, const double* r
 #pragma unroll
         for (int i = 0; i < KR; ++i) r[i] = xs[i];
     }
+    if constexpr (MODE == 3 && Term::FRAME == 1) {
+        hinge_derivs<Term, T>(r, rest, prm, out, in);
+        return;
+    } else if constexpr (MODE == 3 && Term::FRAME == 2) {
+        membrane_derivs<Term, T>(r, rest, prm, out, in);
+        return;
+    } else {
     using S = typename std::conditional<MODE == 1, D1<KR, T>, HD<KR, T>>::type;
     S f;
     if constexpr (Term::NRES > 0) {
@@ -378,7 +676,7 @@ __device__ __forceinline__ void element_derivs(const double* xs, const double* r
             for (int i = 0; i < Packed<KR>::N; ++i) out.hr[i] = f.h[i];
         } else if constexpr (MODE == 3) {
 #pragma unroll
-            for (int i = 0; i < Packed<KR>::N; ++i) Aq[i] = f.h[i];
+            for (int i = 0; i < Packed<KR>::N; ++i) in.A[i] = f.h[i];
         }
         return;
     }
@@ -399,48 +697,93 @@ __device__ __forceinline__ void element_derivs(const double* xs, const double* r
 #pragma unroll
         for (int i = 0; i < KR; ++i)
 #pragma unroll
-            for (int j = i; j < KR; ++j) {
-                const int bi = i / D, ci = i % D, bj = j / D, cj = j % D;
-                T acc = T(0);
-#pragma unroll
-                for (int a = 0; a < NS - 1; ++a) {
-                    const double wa = wmat(a, bi);
-                    if (wa == 0.0) continue;
-#pragma unroll
-                    for (int b = 0; b < NS - 1; ++b) {
-                        const double wb = wmat(b, bj);
-                        if (wb == 0.0) continue;
-                        acc += T(wa * wb) * f.h[Packed<KR>::at(a * D + ci, b * D + cj)];
-                    }
-                }
-                Aq[Packed<KR>::at(i, j)] = acc;
-            }
+            for (int j = i; j < KR; ++j)
+                in.A[Packed<KR>::at(i, j)] = helmert_entry<Term, T>(f.h, i / D, i % D, j / D, j % D);
+    }
     }
 }
 
-// clamp(Hq) = U diag(max(lambda, eps)) U^T into out.hr (U = V diag(dsc)); returns whether the eigen-decomposition
-// converged
-template <class Term, typename T>
-__device__ __forceinline__ bool element_clamp(T (&A)[Packed<Term::KR>::N], double eps, ElemOut<Term, T>& out) {
-    constexpr int KR = Term::KR;
-    T V[KR][KR], dsc[KR];
-    const bool conv = jacobi_eig<KR, T>(A, V, dsc, JacobiTol<T>::sweeps, JacobiTol<T>::tol);
-    const T te = T(eps > 0.0 ? eps : 0.0);
+// C = U diag(max(lambda, floor)) U^T (U = V diag(dsc)) of the symmetric N x N matrix A; returns whether the
+// eigen-decomposition converged
+template <int N, typename T>
+__device__ __forceinline__ bool clamp_matrix(T (&A)[Packed<N>::N], T te, T (&C)[Packed<N>::N]) {
+    T V[N][N], dsc[N];
+    const bool conv = jacobi_eig<N, T>(A, V, dsc, JacobiTol<T>::sweeps, JacobiTol<T>::tol);
 #pragma unroll
-    for (int i = 0; i < Packed<KR>::N; ++i) out.hr[i] = T(0);
+    for (int i = 0; i < Packed<N>::N; ++i) C[i] = T(0);
 #pragma unroll
-    for (int m = 0; m < KR; ++m) {
+    for (int m = 0; m < N; ++m) {
         // eigenvector m is column m of V times dsc[m]: its scale squared goes with the eigenvalue
-        const T lam = A[Packed<KR>::at(m, m)];
+        const T lam = A[Packed<N>::at(m, m)];
         const T lp = (lam > te ? lam : te) * (dsc[m] * dsc[m]);
 #pragma unroll
-        for (int i = 0; i < KR; ++i) {
+        for (int i = 0; i < N; ++i) {
             const T li = lp * V[i][m];
 #pragma unroll
-            for (int j = i; j < KR; ++j) out.hr[Packed<KR>::at(i, j)] += li * V[j][m];
+            for (int j = i; j < N; ++j) C[Packed<N>::at(i, j)] += li * V[j][m];
         }
     }
     return conv;
+}
+
+// the clamped Hessian in Helmert coordinates into out.hr; returns whether the eigen-decomposition converged
+template <class Term, typename T>
+__device__ __forceinline__ bool element_clamp(ClampIn<Term, T>& in, double eps, ElemOut<Term, T>& out) {
+    const T te = T(eps > 0.0 ? eps : 0.0);
+    if constexpr (Term::FRAME == 1) {
+        T C[Packed<8>::N];
+        const bool conv = clamp_matrix<8, T>(in.A, te, C);
+        T P[2][3];
+        complement_rows<T>(in.v, P);
+        auto at = [&](int i, int j) { return C[Packed<8>::at(i, j)]; };
+        T X[3][6];   // u rows against the m (0-2) and n (3-5) columns
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                X[i][j] = P[0][i] * at(hinge_m(j), hinge_u(0)) + P[1][i] * at(hinge_m(j), hinge_u(1));
+                X[i][3 + j] = P[0][i] * at(hinge_n(j), hinge_u(0)) + P[1][i] * at(hinge_n(j), hinge_u(1));
+            }
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = i; j < 3; ++j) {
+                T B[3][3];
+                const T p0 = P[0][i] * at(hinge_u(0), hinge_u(0)) + P[1][i] * at(hinge_u(0), hinge_u(1));
+                const T p1 = P[0][i] * at(hinge_u(0), hinge_u(1)) + P[1][i] * at(hinge_u(1), hinge_u(1));
+                B[0][0] = p0 * P[0][j] + p1 * P[1][j] + te * in.v[i] * in.v[j];
+                B[0][1] = X[i][j];
+                B[1][0] = X[j][i];
+                B[0][2] = X[i][3 + j];
+                B[2][0] = X[j][3 + i];
+                B[1][1] = at(hinge_m(i), hinge_m(j));
+                B[1][2] = at(hinge_n(j), hinge_m(i));
+                B[2][1] = at(hinge_n(i), hinge_m(j));
+                B[2][2] = at(hinge_n(i), hinge_n(j));
+                rotate_block<Term, T>(B, in.R, i, j, out);
+            }
+        return conv;
+    } else if constexpr (Term::FRAME == 2) {
+        T C[Packed<4>::N], N2[3];
+        const bool c4 = clamp_matrix<4, T>(in.A, te, C), c2 = clamp_matrix<2, T>(in.B, te, N2);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = i; j < 2; ++j) {
+                T B[3][3];
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) B[a][b] = C[Packed<4>::at(2 * i + a, 2 * j + b)];
+#pragma unroll
+                for (int a = 0; a < 2; ++a) B[a][2] = B[2][a] = T(0);
+                B[2][2] = N2[Packed<2>::at(i, j)];
+                rotate_block<Term, T>(B, in.R, i, j, out);
+            }
+        return c4 && c2;
+    } else {
+        return clamp_matrix<Term::KR, T>(in.A, te, out.hr);
+    }
 }
 
 // Evaluate one element. MODE: 0 passive, 1 gradient, 2 Hessian, 3 clamped Hessian.
@@ -463,9 +806,9 @@ __device__ __forceinline__ bool element_eval(const double* xs, const double* res
         out.f = Term::template energy<double>(r, rest, prm);
         return true;
     } else {
-        T A[Packed<KR>::N];
-        element_derivs<Term, T, MODE>(xs, rest, prm, out, A);
-        if constexpr (MODE == 3) return element_clamp<Term, T>(A, eps, out);
+        ClampIn<Term, T> in;
+        element_derivs<Term, T, MODE>(xs, rest, prm, out, in);
+        if constexpr (MODE == 3) return element_clamp<Term, T>(in, eps, out);
         return true;
     }
 }

@@ -230,8 +230,8 @@ __device__ __forceinline__ void patch_term(const PatchLaunch& L, const PatchTerm
                 }
             }
             if (!queued) {
-                T Aq[Packed<Term::KR>::N];
-                element_derivs<Term, T, 3>(xs, rest, A.prm, o, Aq);
+                ClampIn<Term, T> in;
+                element_derivs<Term, T, 3>(xs, rest, A.prm, o, in);
                 esum += o.f;
                 {
                     T ga = T(0);
@@ -245,7 +245,7 @@ __device__ __forceinline__ void patch_term(const PatchLaunch& L, const PatchTerm
 #pragma unroll
                         for (int c = 0; c < D; ++c) lds_add(sg + lv[s] * D + c, o.g[s * D + c]);
                 }
-                const bool conv = element_clamp<Term, T>(Aq, L.eps, o);
+                const bool conv = element_clamp<Term, T>(in, L.eps, o);
                 if (sizeof(T) == 4 && !conv) {
                     const int k = atomicAdd(L.fb_count, 1);
                     if (k < L.fb_cap) L.fb_list[k] = ((uint32_t)term << kFbTermShift) | kFbGradDone | (uint32_t)e;

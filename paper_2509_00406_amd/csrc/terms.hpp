@@ -10,6 +10,8 @@
 // map, not an approximation. A term that is not translation invariant (TI =
 // false: the per-vertex inertia) seeds its stencil DOFs themselves, KR = NS*D.
 // NVD: values the term reads per stencil vertex from a caller-owned vertex array.
+// FRAME: structure of the Hessian in a frame of the current element, used by the clamp (element.hpp): 1 a hinge
+// (a function of the dihedral angle alone), 2 a membrane (a function of the triangle's metric r_i . r_j), 0 none.
 #pragma once
 #include "dual.hpp"
 
@@ -35,6 +37,7 @@ template <typename S> __device__ __forceinline__ S dot(const V3<S>& a, const V3<
 // Listing 1: squared edge length. r = x1 - x0.
 struct TermEdgeSqlen {
     static constexpr int NS = 2, D = 3, KR = 3, NREST = 0, NAUX = 0, NPSI = 0, NVD = 0, NRES = 0;
+    static constexpr int FRAME = 0;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double*, const double*) {
         return r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
@@ -45,6 +48,7 @@ struct TermEdgeSqlen {
 // l the rest length. rest = {l^2, 1 / l^2}, params = {k, w}.
 struct TermSpring {
     static constexpr int NS = 2, D = 3, KR = 3, NREST = 2, NAUX = 0, NPSI = 0, NVD = 0, NRES = 0;
+    static constexpr int FRAME = 0;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double* rest, const double* prm) {
         const S q = (r[0] * r[0] + r[1] * r[1] + r[2] * r[2]) * rest[1] + (-1.0);
@@ -57,6 +61,7 @@ struct TermSpring {
 // Per-vertex inputs {m, xhat (3)} come from the caller's vertex array; params = {w, g (3)}.
 struct TermInertia {
     static constexpr int NS = 1, D = 3, KR = 3, NREST = 0, NAUX = 0, NPSI = 0, NVD = 4, NRES = 0;
+    static constexpr int FRAME = 0;
     static constexpr bool TI = false;
     template <typename S> __device__ static S energy(const S* x, const double* in, const double* prm) {
         const double m = in[0], wm = prm[0] * in[0];
@@ -74,6 +79,7 @@ struct TermInertia {
 // {w, x_t} from the caller's per-vertex array. Not translation invariant.
 struct TermResPosition {
     static constexpr int NS = 1, D = 3, KR = 3, NREST = 0, NAUX = 0, NPSI = 0, NVD = 4, NRES = 3;
+    static constexpr int FRAME = 0;
     static constexpr bool TI = false;
     template <typename S> __device__ static void residual(const S* x, const double* in, const double*, S* out) {
         const double sw = sqrt(in[0]);
@@ -90,6 +96,7 @@ struct TermResPosition {
 // Edge-length residual (a least-squares spring): r = sqrt(k) (|x1 - x0| - l), rest = {l}, params = {k}.
 struct TermResEdge {
     static constexpr int NS = 2, D = 3, KR = 3, NREST = 1, NAUX = 0, NPSI = 0, NVD = 0, NRES = 1;
+    static constexpr int FRAME = 0;
     static constexpr bool TI = true;
     template <typename S> __device__ static void residual(const S* r, const double* rest, const double* prm, S* out) {
         out[0] = (dsqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]) + (-rest[0])) * sqrt(prm[0]);
@@ -104,6 +111,7 @@ struct TermResEdge {
 // Sec. 7.6: triangle area 0.5 |(x1 - x0) x (x2 - x0)|.
 struct TermTriArea {
     static constexpr int NS = 3, D = 3, KR = 6, NREST = 0, NAUX = 0, NPSI = 0, NVD = 0, NRES = 0;
+    static constexpr int FRAME = 2;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double*, const double*) {
         const V3<S> a{r[0], r[1], r[2]}, b{r[3], r[4], r[5]};
@@ -116,6 +124,7 @@ struct TermTriArea {
 // rest = {Dm^{-1} row-major (4), rest area}.
 struct TermDirichlet {
     static constexpr int NS = 3, D = 1, KR = 2, NREST = 5, NAUX = 0, NPSI = 0, NVD = 0, NRES = 0;
+    static constexpr int FRAME = 0;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double* rest, const double*) {
         const S g0 = r[0] * rest[0] + r[1] * rest[2];
@@ -128,6 +137,7 @@ struct TermDirichlet {
 // r = (x_b - x_a, x_c - x_a); rest = {Dm^{-1} (4), rest area}; prm = {mu, lambda}.
 struct TermStVK {
     static constexpr int NS = 3, D = 3, KR = 6, NREST = 5, NAUX = 0, NPSI = 0, NVD = 0, NRES = 0;
+    static constexpr int FRAME = 2;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double* rest, const double* prm) {
         const double m00 = rest[0], m01 = rest[1], m10 = rest[2], m11 = rest[3];
@@ -157,6 +167,7 @@ struct TermStVK {
 // r = (e, a, b); rest = {mean rest area, rest dihedral}; prm = {k_b, h}.
 struct TermBending {
     static constexpr int NS = 4, D = 3, KR = 9, NREST = 2, NAUX = 0, NPSI = 0, NVD = 0, NRES = 0;
+    static constexpr int FRAME = 1;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double* rest, const double* prm) {
         const V3<S> e{r[0], r[1], r[2]}, a{r[3], r[4], r[5]}, b{r[6], r[7], r[8]};
@@ -174,6 +185,7 @@ struct TermBending {
 // r = (b - a, c - a) in UV; rest = {Dm^{-1} (4), rest area}.
 struct TermSymDir {
     static constexpr int NS = 3, D = 2, KR = 4, NREST = 5, NAUX = 0, NPSI = 0, NVD = 0, NRES = 0;
+    static constexpr int FRAME = 0;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double* rest, const double*) {
         const double m00 = rest[0], m01 = rest[1], m10 = rest[2], m11 = rest[3];
@@ -218,6 +230,7 @@ __device__ __forceinline__ void shell_features(const S* r, const double* rest, S
 // + lambda/2 (E00 + E11)^2 + k_b/2 (dII00^2 + dII11^2 + 2 dII01^2); prm = {mu, lambda, k_b}.
 struct TermShellTri {
     static constexpr int NS = 3, D = 3, KR = 6, NREST = 8, NAUX = 9, NPSI = 0, NVD = 0, NRES = 0;
+    static constexpr int FRAME = 0;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double* rest, const double* prm) {
         S z[6];
@@ -237,6 +250,7 @@ struct TermShellTri {
 // and Hessian of psi(z(r)) in hyper-dual arithmetic.
 struct TermMLP {
     static constexpr int NS = 3, D = 3, KR = 6, NREST = 8, NAUX = 9, NPSI = 28, NVD = 0, NRES = 0;
+    static constexpr int FRAME = 0;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double* rest, const double*) {
         S z[6];
