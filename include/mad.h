@@ -146,7 +146,9 @@ typedef enum mad_scatter {
 typedef struct mad_options {
     int32_t scatter;         /* mad_scatter; 0 = default (MAD_SCATTER_PATCH) */
     int32_t patch_faces;     /* target faces per patch (Sec. 7.1 patch study); 0 = by term mix: 256 when
-                                every term is a spring, inertia, edge-length or residual term, else 512 */
+                                every term is a spring, inertia, edge-length or residual term, else 512, and
+                                fewer (48 at least) where that leaves the device's compute units without a
+                                patch */
     double spd_eps;          /* eigenvalue floor of MAD_SPD; default 0 (PSD) */
     double degenerate_q;     /* MAD_F32: elements whose triangle quality 4 sqrt(3) A / sum(l^2)
                                 falls below this are evaluated and projected in FP64; 0 = 1e-2 */
@@ -213,8 +215,9 @@ int32_t mad_problem_add_vertex_term(mad_problem *prob, int32_t kind, const doubl
                                     const double *vdata_dev);
 
 /* Build patches, upload element data and build the block pattern on the GPU (Sec. 6.1), once.
- * Starts with the layout of the options; with the patch scatter the launch is persistent unless every
- * term is a spring, inertia, edge-length or residual term (those run one workgroup per patch).
+ * Starts with the layout of the options; with the patch scatter the patches are a queue
+ * (mad_problem_set_layout, persistent = 1) unless every term is a spring, inertia, edge-length or residual term
+ * (those run one workgroup per patch).
  * Synchronises the stream. */
 int32_t mad_problem_finalize(mad_problem *prob, void *stream);
 
@@ -333,10 +336,11 @@ int32_t mad_problem_layout(const mad_problem *prob, int32_t *scatter, int32_t *p
                            int32_t *persistent, int32_t *n_patches, int32_t *wg_waves);
 
 /* Rebuild the evaluation layout of a finalized problem: scatter (mad_scatter), patch_faces target
- * (1 .. 2^20; shrunk until the largest patch fits the LDS budget of the tile), persistent = 1 for one
- * grid sized to the device whose workgroups take patches from a queue (patches in index order within
- * four size classes, the largest first; 2: strictly largest first; patch scatter only), 0 for one
- * workgroup per patch; wg_waves: the tile as in mad_options (0 keeps the current one). The block pattern
+ * (1 .. 2^20; shrunk until nearly every patch fits the LDS budget of the tile, the others halved),
+ * persistent = 1 for the patches as a queue: handed out by the device's dispatcher, or, where one workgroup
+ * fills a compute unit (Hessians of heavy terms in FP64), taken by a grid sized to the device (in index order
+ * within four size classes, the largest first); 2: always such a grid, strictly largest first; patch scatter
+ * only), 0 for one workgroup per patch; wg_waves: the tile as in mad_options (0 keeps the current one). The block pattern
  * and the outputs' layout do not change. Synchronises the stream. On failure the problem is left
  * unusable (MAD_E_STATE on eval). */
 int32_t mad_problem_set_layout(mad_problem *prob, int32_t scatter, int32_t patch_faces, int32_t persistent,

@@ -379,10 +379,9 @@ int32_t mad_problem_finalize(mad_problem* p, void* stream) {
     }
     // element order first (the pattern is built from the device stencils), then the pattern, then
     // the scatter structures that index into it
-    // default patch target: smaller patches for cheap elements (more workgroups to hide their latency)
-    if (p->opt.patch_faces == 0) p->opt.patch_faces = p->light ? 256 : 512;
-    // default launch: the persistent grid for the patch scatter of heavy elements (a workgroup's
-    // flush of one patch overlaps its next patch's work); one workgroup per patch for light terms
+    if (p->opt.patch_faces == 0) p->opt.patch_faces = default_patch_faces(m.nt, p->n_cu, p->light);
+    // default launch: the patches as a queue for the patch scatter of heavy elements, one workgroup per patch
+    // for light terms
     const int persistent = (p->scatter == MAD_SCATTER_PATCH && !p->light) ? 1 : 0;
     if ((rc = build_layout(p, p->opt.patch_faces, p->scatter, persistent, s)) != MAD_OK) return rc;
     std::vector<PatternTerm> pts;

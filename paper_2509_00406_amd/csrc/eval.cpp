@@ -53,9 +53,17 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
         if (mode & MAD_HESS) MAD_HIP_TRY(launch_fill(hess, p->nnzb * d * d, eb, s));
         if (hvp) MAD_HIP_TRY(launch_fill(y, m.nv * d, eb, s));
     }
-    // the FP64 redo queue's count and the persistent queue's head, cleared by one small kernel
-    MAD_HIP_TRY(launch_zero_counters(fallback_pass ? sc.fb_count : nullptr,
-                                     (p->scatter == MAD_SCATTER_PATCH && p->persistent) ? sc.work_counter : nullptr, s));
+    const int kmode = (hvp || (mode & MAD_HESS)) ? ((mode & MAD_SPD) ? 3 : 2) : ((mode & MAD_GRAD) ? 1 : 0);
+    // Who hands out the patches of a queued (persistent) layout. The Hessian kernels of heavy terms in FP64 hold
+    // a compute unit's registers with one workgroup, so a unit idles between two of them: there a grid of one
+    // workgroup per unit takes patches from a counter (708^2 shell 1.90 ms, one workgroup per patch 1.96).
+    // Elsewhere several workgroups share a unit and the dispatcher is the queue: the counter's round trips to
+    // memory, shared by all units, cost more than they gain (1024^2 shell FP32 1.37 -> 1.33 ms, 700 spheres
+    // 2.76 -> 2.57, 1001^2 symmetric Dirichlet 225 -> 216 us, 200^2 Dirichlet FP64 26 -> 21 us).
+    const bool queue = p->scatter == MAD_SCATTER_PATCH &&
+                       (p->persistent == 2 || (p->persistent == 1 && p->prec == MAD_F64 && d == 3 && !p->light && kmode >= 2));
+    // the FP64 redo queue's count and the patch queue's head, cleared by one small kernel
+    MAD_HIP_TRY(launch_zero_counters(fallback_pass ? sc.fb_count : nullptr, queue ? sc.work_counter : nullptr, s));
     if (ev) MAD_HIP_TRY(hipEventRecord((*ev)[1], s));
     // learned and analytic shell densities: vertex normals of x, then the network pass per MLP term
     if (p->shell) MAD_HIP_TRY(launch_vertex_normals(x, m.nv, p->d_vf_ptr, p->d_vf, p->d_tris, sc.normals, s));
@@ -77,7 +85,6 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
         MAD_HIP_TRY(launch_mlp_head(H, s));
     }
     if (ev) MAD_HIP_TRY(hipEventRecord((*ev)[2], s));
-    const int kmode = (hvp || (mode & MAD_HESS)) ? ((mode & MAD_SPD) ? 3 : 2) : ((mode & MAD_GRAD) ? 1 : 0);
     const int np = p->patches.n;
     int n_partial_terms = (int)p->terms.size();
     if (p->scatter == MAD_SCATTER_PATCH) {
@@ -111,7 +118,7 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
         L.qmin = p->opt.degenerate_q;
         L.lock_spins = p->opt.lock_spins == MAD_LOCK_NO_WAIT ? 0
                        : (p->opt.lock_spins > 0 ? p->opt.lock_spins : kDefaultLockSpins);
-        L.persistent = p->persistent;
+        L.persistent = queue ? 1 : 0;
         L.block = (p->wg_waves == 8 && p->prec == MAD_F32) ? 512 : 256;
         L.work_order = p->d_work_order;
         L.work_counter = sc.work_counter;

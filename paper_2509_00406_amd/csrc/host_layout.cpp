@@ -87,9 +87,11 @@ void order_terms(mad_problem* p) {
 }
 
 // largest per-patch vertex and upper-block counts of the current patching (patches split over threads)
-void patch_extent(const mad_problem* p, int32_t* max_lv, int32_t* max_lb) {
+void patch_extent(const mad_problem* p, int32_t* max_lv, int32_t* max_lb,
+                  std::vector<std::pair<int32_t, int32_t>>* each) {
     const int64_t nv = p->mesh->nv;
     const int32_t np = p->patches.n;
+    if (each) each->assign((size_t)np, {0, 0});
     const int nth = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
     std::vector<int32_t> mv_t((size_t)nth, 0), mb_t((size_t)nth, 0);
     // Per patch: distinct vertices through a per-thread vertex map (first-seen local numbers), distinct upper
@@ -147,6 +149,7 @@ void patch_extent(const mad_problem* p, int32_t* max_lv, int32_t* max_lb) {
                 nblocks = (int32_t)(std::unique(keys.begin(), keys.end()) - keys.begin());
             }
             for (int32_t v : verts) loc[v] = -1;
+            if (each) (*each)[(size_t)q] = {nloc, nblocks};
             mv = std::max(mv, nloc);
             mb = std::max(mb, nblocks);
         }

@@ -486,8 +486,9 @@ __device__ __forceinline__ void eval_patch_one(const PatchLaunch& L, int p, unsi
     block_sum_store(red, L.partial + p);
 }
 
-// One patch per workgroup, or (persistent) a grid sized to the device whose workgroups take
-// patches from a counter in the given order (largest first) until every patch is taken.
+// One patch per workgroup, or (persistent) a grid sized to the device whose workgroups take their first
+// patch by their own number and the following ones from a counter, in the given order (largest first). The
+// next number is asked for before a patch is worked on, so its round trip to memory is not waited for.
 template <typename T, int MODE, int D, int FAM, int BLK>
 __device__ __forceinline__ void eval_patch_body(const PatchLaunch& L) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -498,14 +499,15 @@ __device__ __forceinline__ void eval_patch_body(const PatchLaunch& L) {
         eval_patch_one<T, MODE, D, FAM, BLK>(L, blockIdx.x, smem, red, &unit_next, &block_lock, term_range);
         return;
     }
-    for (;;) {
-        if (threadIdx.x == 0) next = atomicAdd(L.work_counter, 1);
-        __syncthreads();
-        const int k = next;
-        __syncthreads();   // every lane has read `next` before it is overwritten
-        if (k >= L.n_patch) break;
+    int k = blockIdx.x;
+    while (k < L.n_patch) {
+        int after = 0;
+        if (threadIdx.x == 0) after = (int)gridDim.x + atomicAdd(L.work_counter, 1);
         eval_patch_one<T, MODE, D, FAM, BLK>(L, L.work_order[k], smem, red, &unit_next, &block_lock, term_range);
+        if (threadIdx.x == 0) next = after;
         __syncthreads();   // the flush has read LDS before the next patch clears it
+        k = next;
+        __syncthreads();   // every lane has read `next` before it is overwritten
     }
 }
 

@@ -81,6 +81,9 @@ struct Patches {
     int32_t n = 0;
     std::vector<int32_t> face_patch;     // [nt]
     std::vector<int32_t> comp_patch_ptr; // [ncomp + 1]
+    std::vector<int32_t> order, start;   // faces patch by patch, first position of every patch (and the end)
+    std::vector<int32_t> comp_face;      // [ncomp + 1] first position of every component
+    std::vector<int32_t> coarse_order, coarse_start;   // after the first cuts, kept for rebuilds with another target
 };
 
 // scratch of the pattern update for new interaction pairs, sized at finalize from the reserve
@@ -207,11 +210,17 @@ int rest_shell(const mad_mesh& m, const double* rest_pos, std::vector<double>& o
 int rest_spring(const mad_mesh& m, const double* rest_pos, std::vector<double>& out);     // [ne][2]
 int rest_edge_length(const mad_mesh& m, const double* rest_pos, std::vector<double>& out);  // [ne]
 void build_patches(const mad_mesh& m, int target_faces, Patches& p);
+// cuts the patches marked in `which` in two
+void halve_patches(const mad_mesh& m, const std::vector<uint8_t>& which, Patches& p);
+// layout.cpp: the default patch target
+int default_patch_faces(int64_t n_faces, int n_cu, bool light);
 // host_layout.cpp: element order by patch, colour order inside patches, the largest patch's vertex and
 // upper-block counts, segments of the 64-element work units
 void order_terms(mad_problem* p);
 void color_within_patches(Term& t, int64_t nv);
-void patch_extent(const mad_problem* p, int32_t* max_lv, int32_t* max_lb);
+// each (may be NULL): those of every patch
+void patch_extent(const mad_problem* p, int32_t* max_lv, int32_t* max_lb,
+                  std::vector<std::pair<int32_t, int32_t>>* each = nullptr);
 void unit_segments(const Term& t, int32_t np, int64_t nv, std::vector<uint8_t>& seg);
 // colored scatter: greedy coloring of each term's elements (no shared vertex within a color), elements
 // sorted by color then component, chunks, energy slots; comp_slot_ptr [n_comp + 1] (host)
