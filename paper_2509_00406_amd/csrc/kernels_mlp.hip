@@ -150,49 +150,66 @@ __device__ __forceinline__ void split3(float v, bf16x8& h, bf16x8& m, bf16x8& l,
 // u = W2^T v, the network's derivatives with respect to the scaled features xh are
 //   dpsi/dxh_i        = sum_k u_k sigma(a1_k) W1[k,i]
 //   d2psi/dxh_i dxh_j = sum_k u_k sigma'(a1_k) W1[k,i] W1[k,j] + sum_m w3_m sigma'(a2_m) g_mi g_mj,
-// g_mi = sum_k W2[m,k] sigma(a1_k) W1[k,i] (layer 2's first-order channels). Three groups of contractions run
+// g_mi = sum_k W2[m,k] W1[k,i] sigma(a1_k) (layer 2's first-order channels). Four groups of contractions run
 // on the matrix cores (v_mfma_f32_16x16x32_bf16):
-//   a2 - b2 = W2 sp(a1), g_i = W2 (sigma(a1) W1[:,i])   W2 exact in BF16 (held in registers as the A operand),
-//                                                      the seven activation channels in three BF16 terms;
-//   u = W2^T v                                         v in three BF16 terms, W2^T read from LDS;
-//   S1[t,q] = sum_k (u sigma') C[k,q]                  C[k,q] = W1[k,i_q] W1[k,j_q] over the 21 packed pairs, a
-//                                                      product of two BF16 values (16 significant bits: exactly
-//                                                      two BF16 terms), built once per workgroup in LDS; u sigma'
-//                                                      in three terms: the layer-1 part of the second derivatives.
+//   a2 - b2 = W2 sp(a1)            W2 exact in BF16, sp(a1) in three BF16 terms;
+//   g_i = G_i sigma(a1)            G_i[m,k] = W2[m,k] W1[k,i], a product of two BF16 values (16 significant
+//                                  bits: exactly two BF16 terms); sigma(a1) in three terms, split once for the
+//                                  six channels;
+//   u = W2^T v                     v in three BF16 terms;
+//   S1[t,q] = sum_k (u sigma') C[k,q]   C[k,q] = W1[k,i_q] W1[k,j_q] over the 21 packed pairs, two BF16 terms;
+//                                  u sigma' in three: the layer-1 part of the second derivatives.
 // A product of three-term by two-term operands drops only the lo x lo part (2^-24 relative), so every
 // contraction reproduces FP32 products with FP32 accumulation. The layer-2 part of the second derivatives (a
-// rank-6 sum per triangle) and the first derivatives are per-triangle VALU work. (Moving the six first-order
-// channels to constant operands G_i = W2 diag(W1[:,i]) in LDS, split once, cut the VALU instructions by a
-// quarter but ran slower: at one wave per SIMD the extra MFMA chains and LDS reads were not hidden.)
+// rank-6 sum per triangle) and the first derivatives are per-triangle VALU work.
+//
+// The constant operands (W2, W2^T, G, C) are built once per workgroup and fill the CU's LDS together with the
+// waves' tiles, so that the forward channels need no operand of their own per triangle and a wave's state (one
+// quarter of layer 2 at a time) fits half of a SIMD's registers: two waves per SIMD, one's vector instructions
+// under the other's matrix instructions and latencies. 999,698 triangles: 569 us when each channel's activations
+// were split on their own and one wave per SIMD held all of layer 2, 440 us now (2,110 vector and 308 matrix
+// instructions a tile instead of 3,990 and 212): about 80% of the cycles issue a vector instruction. Unrolling the
+// quarters of layer 2, or computing one quarter while another is finished, spilled or was slower.
 // Layouts (16x16x32 MFMA): B operand lane l holds column l % 16 and k = 32 ks + 8 (l / 16) + j; A operand lane
 // l holds row l % 16 and the same k; accumulators hold rows 4 (l / 16) + jj of column l % 16.
-constexpr int kHeadWaves = 4;
-constexpr int kLdsRow = kHid + 8;   // BF16 row stride of the LDS operand tables (144 B: 16-byte reads spread over banks)
+constexpr int kHeadWaves = 8;
+constexpr int kTileRow = kHid + 1;   // floats of a tile's row in LDS
 
 struct HeadSmem {   // byte offsets into the network pass's dynamic LDS
     static constexpr int w1 = 0;                                   // float [64][6]
     static constexpr int b1 = w1 + kHid * 6 * 4;                   // float [64]
     static constexpr int b2 = b1 + kHid * 4;
     static constexpr int w3 = b2 + kHid * 4;
-    static constexpr int w2t = w3 + kHid * 4;                      // bf16 [k][kLdsRow]: W2 transposed
-    static constexpr int c = w2t + kHid * kLdsRow * 2;             // bf16 [2][32][kLdsRow]: C hi, lo (q >= 21: 0)
-    static constexpr int t = c + 2 * 32 * kLdsRow * 2;             // float [waves][16][kHid + 1]
-    static constexpr int bytes = t + kHeadWaves * 16 * (kHid + 1) * 4;
+    static constexpr int w2 = w3 + kHid * 4;                       // bf16 [m][64], rows swizzled (below)
+    static constexpr int w2t = w2 + kHid * kHid * 2;               // bf16 [k][64]: W2 transposed
+    static constexpr int c = w2t + kHid * kHid * 2;                // bf16 [2][32][64]: C hi, lo (q >= 21: 0)
+    static constexpr int g = c + 2 * 32 * kHid * 2;                // bf16 [6][2][m][64]: G hi, lo
+    static constexpr int t = g + 6 * 2 * kHid * kHid * 2;          // float [waves][16][kTileRow]
+    static constexpr int bytes = t + kHeadWaves * 16 * kTileRow * 4;
 };
-static_assert(HeadSmem::w2t % 16 == 0 && HeadSmem::c % 16 == 0 && HeadSmem::t % 16 == 0,
-              "16-byte LDS operand reads");
+static_assert(HeadSmem::w2 % 16 == 0 && HeadSmem::t % 16 == 0, "16-byte LDS operand reads");
 static_assert(HeadSmem::bytes <= 160 * 1024, "network pass LDS fits a CU");
-static_assert(kOffW2 % 8 == 0 && kHid % 8 == 0, "16-byte reads of W2 rows from the BF16 parameters");
 
-// a product of two BF16 values (exact in FP32) as hi + lo BF16 terms, both exact
-__device__ __forceinline__ void split2_exact(float p, uint16_t& hi, uint16_t& lo) {
-    hi = f2bf(p);
-    lo = f2bf(p - bf2f(hi));
-}
+// element of (row, k) in an LDS table of 64-element BF16 rows: the row's eight 16-byte pieces are permuted by
+// its number, so that the 16 rows a wave reads at one k lie in different banks
+__device__ __forceinline__ int head_at(int row, int k) { return row * kHid + ((((k >> 3) ^ (row >> 1)) & 7) << 3) + (k & 7); }
 
-__device__ __forceinline__ bf16x8 lds_bf16x8(const uint16_t* p) {
+__device__ __forceinline__ bf16x8 lds_bf16x8(const __bf16* p) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const short8*>(p));
 }
+
+// rows a, b, c, d of four per-lane values summed over the four 16-lane groups: group g gets the g-th value's sum
+__device__ __forceinline__ float group_sums(float a, float b, float c, float d) {
+    auto bits = [](float f) { return __float_as_uint(f); };
+    const auto ab = __builtin_amdgcn_permlane16_swap(bits(a), bits(b), false, false);
+    const auto cd = __builtin_amdgcn_permlane16_swap(bits(c), bits(d), false, false);
+    const float p = __uint_as_float(ab[0]) + __uint_as_float(ab[1]);
+    const float q = __uint_as_float(cd[0]) + __uint_as_float(cd[1]);
+    const auto pq = __builtin_amdgcn_permlane32_swap(bits(p), bits(q), false, false);
+    return __uint_as_float(pq[0]) + __uint_as_float(pq[1]);
+}
+
+#define MAD_MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0)
 
 __global__ __launch_bounds__(kHeadWaves * 64) void k_mlp_head(MlpHeadLaunch L) {
     extern __shared__ __align__(16) unsigned char head_smem[];
@@ -200,36 +217,56 @@ __global__ __launch_bounds__(kHeadWaves * 64) void k_mlp_head(MlpHeadLaunch L) {
     float* sB1 = reinterpret_cast<float*>(head_smem + HeadSmem::b1);
     float* sB2 = reinterpret_cast<float*>(head_smem + HeadSmem::b2);
     float* sW3 = reinterpret_cast<float*>(head_smem + HeadSmem::w3);
-    uint16_t* sW2T = reinterpret_cast<uint16_t*>(head_smem + HeadSmem::w2t);
-    uint16_t* sC = reinterpret_cast<uint16_t*>(head_smem + HeadSmem::c);
+    __bf16* sW2 = reinterpret_cast<__bf16*>(head_smem + HeadSmem::w2);
+    __bf16* sW2T = reinterpret_cast<__bf16*>(head_smem + HeadSmem::w2t);
+    __bf16* sC = reinterpret_cast<__bf16*>(head_smem + HeadSmem::c);
+    __bf16* sG = reinterpret_cast<__bf16*>(head_smem + HeadSmem::g);
     for (int i = threadIdx.x; i < kHid * 6; i += blockDim.x) sW1[i] = bf2f(L.wbf[kOffW1 + i]);
     for (int i = threadIdx.x; i < kHid; i += blockDim.x) {
         sB1[i] = bf2f(L.wbf[kOffB1 + i]);
         sB2[i] = bf2f(L.wbf[kOffB2 + i]);
         sW3[i] = bf2f(L.wbf[kOffW3 + i]);
     }
-    for (int idx = threadIdx.x; idx < kHid * kHid; idx += blockDim.x)
-        sW2T[(idx % kHid) * kLdsRow + idx / kHid] = L.wbf[kOffW2 + idx];
+    __syncthreads();
+    // a product of two BF16 values, exact in FP32, is exactly two BF16 terms
+    for (int idx = threadIdx.x; idx < kHid * kHid; idx += blockDim.x) {
+        const int m = idx / kHid, k = idx % kHid, at = head_at(m, k);
+        const float w2 = bf2f(L.wbf[kOffW2 + idx]);
+        sW2[at] = (__bf16)w2;
+        sW2T[head_at(k, m)] = (__bf16)w2;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            const float p = w2 * sW1[k * 6 + i];
+            const __bf16 hi = (__bf16)p;
+            sG[(2 * i) * kHid * kHid + at] = hi;
+            sG[(2 * i + 1) * kHid * kHid + at] = (__bf16)(p - (float)hi);
+        }
+    }
     for (int idx = threadIdx.x; idx < 32 * kHid; idx += blockDim.x) {
         const int q = idx / kHid, k = idx % kHid;
-        const float p = q < 21 ? bf2f(L.wbf[kOffW1 + k * 6 + pair_i(q)]) * bf2f(L.wbf[kOffW1 + k * 6 + pair_j(q)]) : 0.0f;
-        uint16_t hi, lo;
-        split2_exact(p, hi, lo);
-        sC[(0 * 32 + q) * kLdsRow + k] = hi;
-        sC[(1 * 32 + q) * kLdsRow + k] = lo;
+        const float p = q < 21 ? sW1[k * 6 + pair_i(q)] * sW1[k * 6 + pair_j(q)] : 0.0f;
+        const __bf16 hi = (__bf16)p;
+        sC[head_at(q, k)] = hi;
+        sC[32 * kHid + head_at(q, k)] = (__bf16)(p - (float)hi);
     }
     __syncthreads();
     const float b3 = bf2f(L.wbf[kOffB3]);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, col = lane & 15;
-    float (*T)[kHid + 1] = reinterpret_cast<float (*)[kHid + 1]>(head_smem + HeadSmem::t) + wave * 16;
-    // A operand (all seven forward channels): W2 rows m = 16 mt + col, k = 32 ks + 8 g + j, as 16-byte global
-    // reads (the BF16 parameters are their own allocation, and kOffW2 and every row start are multiples of 8)
-    short8 A[4][2];
+    float (*T)[kTileRow] = reinterpret_cast<float (*)[kTileRow]>(head_smem + HeadSmem::t) + wave * 16;
+    // back to z: psi scales by s_out, dpsi/dz_i by s_out s_in[i], the second derivatives by both inputs' scales;
+    // this lane's outputs are 4 k + g of (psi, 6 first, 21 second derivatives)
+    float sc[7];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-            A[mt][ks] = *reinterpret_cast<const short8*>(L.wbf + kOffW2 + (16 * mt + col) * kHid + 32 * ks + 8 * g);
+    for (int k = 0; k < 7; ++k) {
+        const int o = 4 * k + g;
+        float f = L.s_out;
+        for (int i = 0; i < 6; ++i) {
+            if (o == 1 + i) f *= L.s_in[i];
+            for (int j = i; j < 6; ++j)
+                if (o == 7 + Packed<6>::at(i, j)) f *= L.s_in[i] * L.s_in[j];
+        }
+        sc[k] = f;
+    }
     const int64_t tiles = (L.n + 15) / 16;
     for (int64_t tile = (int64_t)blockIdx.x * kHeadWaves + wave; tile < tiles;
          tile += (int64_t)gridDim.x * kHeadWaves) {
@@ -240,7 +277,7 @@ __global__ __launch_bounds__(kHeadWaves * 64) void k_mlp_head(MlpHeadLaunch L) {
         for (int i = 0; i < 6; ++i) xh[i] = valid ? L.xh[(int64_t)i * L.n + e] : 0.0f;
         // layer 1 at this lane's 16 units (B layout): sp(a1) and sigma(a1), each split into three BF16 terms
         float s1[2][8];
-        bf16x8 b0h[2], b0m[2], b0l[2];
+        bf16x8 p0[2][3], sg[2][3];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -249,76 +286,59 @@ __global__ __launch_bounds__(kHeadWaves * 64) void k_mlp_head(MlpHeadLaunch L) {
                 float a = sB1[k];
 #pragma unroll
                 for (int i = 0; i < 6; ++i) a = fmaf(sW1[k * 6 + i], xh[i], a);
-                float sp, sg;
-                softplus_logistic(a, sp, sg);
-                s1[ks][j] = sg;
-                split3(sp, b0h[ks], b0m[ks], b0l[ks], j);
+                float sp;
+                softplus_logistic(a, sp, s1[ks][j]);
+                split3(sp, p0[ks][0], p0[ks][1], p0[ks][2], j);
+                split3(s1[ks][j], sg[ks][0], sg[ks][1], sg[ks][2], j);
             }
-        // channel 0: the value through layer 2
-        float P0 = 0.0f, PH[21];
+        // layer 2, 16 units at a time: the value and the six first-order channels, then everything that needs
+        // them (v to LDS as [triangle][unit])
+        float P[28];   // psi, first derivatives, packed second derivatives: this lane's part of the sums
 #pragma unroll
-        for (int q = 0; q < 21; ++q) PH[q] = 0.0f;
-        float v[4][4], ws2p[4][4], a2g[6][4][4];
-#pragma unroll
+        for (int q = 0; q < 28; ++q) P[q] = 0.0f;
+#pragma unroll 1
         for (int mt = 0; mt < 4; ++mt) {
-            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+            const int row = 16 * mt + col;
+            f32x4 val = {0.0f, 0.0f, 0.0f, 0.0f}, ch[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) ch[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                const bf16x8 a = __builtin_bit_cast(bf16x8, A[mt][ks]);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0h[ks], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0m[ks], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0l[ks], acc, 0, 0, 0);
+                const int at = head_at(row, 32 * ks + 8 * g);
+                const bf16x8 a = lds_bf16x8(sW2 + at);
+#pragma unroll
+                for (int r = 0; r < 3; ++r) val = MAD_MFMA(a, p0[ks][r], val);
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    const bf16x8 hi = lds_bf16x8(sG + (2 * i) * kHid * kHid + at);
+                    const bf16x8 lo = lds_bf16x8(sG + (2 * i + 1) * kHid * kHid + at);
+                    ch[i] = MAD_MFMA(hi, sg[ks][0], ch[i]);
+                    ch[i] = MAD_MFMA(hi, sg[ks][1], ch[i]);
+                    ch[i] = MAD_MFMA(hi, sg[ks][2], ch[i]);
+                    ch[i] = MAD_MFMA(lo, sg[ks][0], ch[i]);
+                    ch[i] = MAD_MFMA(lo, sg[ks][1], ch[i]);
+                }
             }
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 const int m = 16 * mt + 4 * g + jj;
-                const float a2 = acc[jj] + sB2[m];
-                float sp, sg;
-                softplus_logistic(a2, sp, sg);
-                v[mt][jj] = sW3[m] * sg;
-                ws2p[mt][jj] = sW3[m] * sg * (1.0f - sg);
-                P0 = fmaf(sW3[m], sp, P0);
-            }
-        }
-        // channels 1..6: g_i = W2 (sigma(a1) W1[:,i]), the B operand split per channel
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            bf16x8 bh[2], bm[2], bl[2];
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) split3(s1[ks][j] * sW1[(32 * ks + 8 * g + j) * 6 + i], bh[ks], bm[ks], bl[ks], j);
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const bf16x8 a = __builtin_bit_cast(bf16x8, A[mt][ks]);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bh[ks], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bm[ks], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl[ks], acc, 0, 0, 0);
-                }
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) a2g[i][mt][jj] = acc[jj];
-            }
-        }
-        // second-order part through layer 2's nonlinearity: sum_m w3 sigma'(a2) g_mi g_mj
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
+                const float w3 = sW3[m];
+                float sp, s2;
+                softplus_logistic(val[jj] + sB2[m], sp, s2);
+                const float v = w3 * s2;
+                T[col][m] = v;
+                P[0] = fmaf(w3, sp, P[0]);
+                const float c2 = v * (1.0f - s2);
 #pragma unroll
                 for (int i = 0; i < 6; ++i) {
-                    const float t = ws2p[mt][jj] * a2g[i][mt][jj];
+                    const float t = c2 * ch[i][jj];
 #pragma unroll
-                    for (int j2 = i; j2 < 6; ++j2) PH[Packed<6>::at(i, j2)] = fmaf(t, a2g[j2][mt][jj], PH[Packed<6>::at(i, j2)]);
+                    for (int j = i; j < 6; ++j)
+                        P[7 + Packed<6>::at(i, j)] = fmaf(t, ch[j][jj], P[7 + Packed<6>::at(i, j)]);
                 }
             }
-        // u = W2^T v: v to LDS as [triangle][unit], read back as the A operand (rows = triangles)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) T[col][16 * mt + 4 * g + jj] = v[mt][jj];
+        }
+        // u = W2^T v: v read back as the A operand (rows = triangles)
         wave_sync();
         bf16x8 vh[2], vm[2], vl[2];
 #pragma unroll
@@ -332,10 +352,10 @@ __global__ __launch_bounds__(kHeadWaves * 64) void k_mlp_head(MlpHeadLaunch L) {
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
                 // B operand: W2[m][k], m = 32 ks + 8 g + j, k = 16 nt + col (a row of W2^T)
-                const bf16x8 b = lds_bf16x8(sW2T + (16 * nt + col) * kLdsRow + 32 * ks + 8 * g);
-                U[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vh[ks], b, U[nt], 0, 0, 0);
-                U[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vm[ks], b, U[nt], 0, 0, 0);
-                U[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vl[ks], b, U[nt], 0, 0, 0);
+                const bf16x8 b = lds_bf16x8(sW2T + head_at(16 * nt + col, 32 * ks + 8 * g));
+                U[nt] = MAD_MFMA(vh[ks], b, U[nt]);
+                U[nt] = MAD_MFMA(vm[ks], b, U[nt]);
+                U[nt] = MAD_MFMA(vl[ks], b, U[nt]);
             }
         }
         wave_sync();   // every lane has read v before u overwrites it
@@ -346,17 +366,15 @@ __global__ __launch_bounds__(kHeadWaves * 64) void k_mlp_head(MlpHeadLaunch L) {
         wave_sync();
         // first derivatives over this lane's 16 units; u sigma' split as the A operand of the layer-1
         // second-order contraction (rows = triangles, the same lane distribution as the B layout)
-        float Pg[6] = {0, 0, 0, 0, 0, 0};
         bf16x8 uh[2], um[2], ul[2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int k = 32 * ks + 8 * g + j;
-                const float u = T[col][k];
-                const float us = u * s1[ks][j];
+                const float us = T[col][k] * s1[ks][j];
 #pragma unroll
-                for (int i = 0; i < 6; ++i) Pg[i] = fmaf(us, sW1[k * 6 + i], Pg[i]);
+                for (int i = 0; i < 6; ++i) P[1 + i] = fmaf(us, sW1[k * 6 + i], P[1 + i]);
                 split3(us * (1.0f - s1[ks][j]), uh[ks], um[ks], ul[ks], j);
             }
         f32x4 S1[2];
@@ -365,58 +383,33 @@ __global__ __launch_bounds__(kHeadWaves * 64) void k_mlp_head(MlpHeadLaunch L) {
             S1[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                const uint16_t* crow = sC + (16 * nt + col) * kLdsRow + 32 * ks + 8 * g;
-                const bf16x8 ch = lds_bf16x8(crow), cl = lds_bf16x8(crow + 32 * kLdsRow);
-                S1[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(uh[ks], ch, S1[nt], 0, 0, 0);
-                S1[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(um[ks], ch, S1[nt], 0, 0, 0);
-                S1[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ul[ks], ch, S1[nt], 0, 0, 0);
-                S1[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(uh[ks], cl, S1[nt], 0, 0, 0);
-                S1[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(um[ks], cl, S1[nt], 0, 0, 0);
+                const int at = head_at(16 * nt + col, 32 * ks + 8 * g);
+                const bf16x8 hi = lds_bf16x8(sC + at), lo = lds_bf16x8(sC + 32 * kHid + at);
+                S1[nt] = MAD_MFMA(uh[ks], hi, S1[nt]);
+                S1[nt] = MAD_MFMA(um[ks], hi, S1[nt]);
+                S1[nt] = MAD_MFMA(ul[ks], hi, S1[nt]);
+                S1[nt] = MAD_MFMA(uh[ks], lo, S1[nt]);
+                S1[nt] = MAD_MFMA(um[ks], lo, S1[nt]);
             }
         }
-        wave_sync();   // u is read before the layer-2 second derivatives overwrite it
-        // sum over the four lanes holding the same triangle
-        P0 += __shfl_xor(P0, 16);
-        P0 += __shfl_xor(P0, 32);
+        wave_sync();   // u is read before the layer-1 second derivatives overwrite it
 #pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            Pg[i] += __shfl_xor(Pg[i], 16);
-            Pg[i] += __shfl_xor(Pg[i], 32);
-        }
+        for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-        for (int q = 0; q < 21; ++q) {
-            PH[q] += __shfl_xor(PH[q], 16);
-            PH[q] += __shfl_xor(PH[q], 32);
-        }
-        if (g == 0) {
-#pragma unroll
-            for (int q = 0; q < 21; ++q) T[col][q] = PH[q];
-        }
-        if (valid && g == 0) {
-            // back to z: dpsi/dz_i = s_out s_in[i] dpsi/dxh_i, likewise for the second derivatives
-            L.psi[e] = L.s_out * (P0 + b3);
-#pragma unroll
-            for (int i = 0; i < 6; ++i) L.psi[(int64_t)(1 + i) * L.n + e] = L.s_out * L.s_in[i] * Pg[i];
-        }
+            for (int jj = 0; jj < 4; ++jj) T[4 * g + jj][16 * nt + col] = S1[nt][jj];
         wave_sync();
-        // second derivatives: the layer-1 part (S1 rows = triangles 4 g + jj, column q = 16 nt + col) plus
-        // the layer-2 part from LDS
+        // sums over the four lanes holding the same triangle; each writes seven of its 28 outputs
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int q = 16 * nt + col;
-            if (q < 21) {
-                const float sc = L.s_out * L.s_in[pair_i(q)] * L.s_in[pair_j(q)];
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    const int t = 4 * g + jj;
-                    const int64_t et = tile * 16 + t;
-                    if (et < L.n) L.psi[(int64_t)(7 + q) * L.n + et] = sc * (S1[nt][jj] + T[t][q]);
-                }
-            }
+        for (int k = 0; k < 7; ++k) {
+            const int o = 4 * k + g;
+            float r = group_sums(P[4 * k], P[4 * k + 1], P[4 * k + 2], P[4 * k + 3]);
+            r += o == 0 ? b3 : o >= 7 ? T[col][o - 7] : 0.0f;
+            if (valid) L.psi[(int64_t)o * L.n + e] = sc[k] * r;
         }
-        wave_sync();   // the layer-2 part is read before the next tile writes v
+        wave_sync();   // the layer-1 part is read before the next tile writes v
     }
 }
+#undef MAD_MFMA
 
 __global__ __launch_bounds__(256) void k_mlp_features(MlpHeadLaunch L) {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < L.n; e += (int64_t)gridDim.x * blockDim.x) {
