@@ -135,7 +135,10 @@ typedef enum mad_scatter {
                                 in LDS, element contributions summed in LDS, then every entry written
                                 once: by its patch if no other patch touches it, else by a gather
                                 kernel summing the patches' partials in a fixed order. No global
-                                atomics and no zero fill of the outputs. */
+                                atomics and no zero fill of the outputs. Problems of edge and vertex terms only
+                                are evaluated by block rows instead: a row computes the edges around its vertex
+                                and writes its gradient entry and blocks, bitwise reproducible; the patch
+                                settings below do not change their launch. */
     MAD_SCATTER_COLOR = 3    /* the coloring alternative of Sec. 5.5: each term's elements greedily
                                 colored so that no two elements of a color share a vertex, one launch
                                 per color and term, each element adding its entries into pre-zeroed
@@ -158,9 +161,8 @@ typedef struct mad_options {
                                 without the lock) and raises the internal-error flag, so mad_problem_status
                                 returns MAD_E_INTERNAL; the kernels still run to completion */
     int32_t wg_waves;        /* tile of the patch kernels: waves (64 lanes) per workgroup, 0 = 4 (default), 4
-                                or 8 (MAD_F32 only; MAD_F64 keeps 4). With 8, a workgroup of terms other than
-                                the light ones (springs, inertia, edge lengths, residuals) has the CU's LDS to
-                                itself (148 KB: larger patches); light terms keep 76 KB per workgroup */
+                                or 8 (MAD_F32 only; MAD_F64 keeps 4). With 8, a workgroup has the CU's LDS to
+                                itself (148 KB: larger patches) */
     int32_t reserved[6];     /* must be zero */
 } mad_options;
 

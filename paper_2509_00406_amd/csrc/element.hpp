@@ -348,11 +348,18 @@ template <class Term, typename T>
 struct ClampIn<Term, T, 2> {
     T A[Packed<4>::N], B[3], R[3][3];
 };
+template <class Term, typename T>
+struct ClampIn<Term, T, 3> {
+    T along, across, u[3];
+};
 
 // ---- clamp in a frame of the element ----------------------------------------------------------
 // Turning the element turns its Hessian, so the derivatives can be taken in orthonormal axes (u, m, n) of the
 // current element, where most coordinates vanish (the compiler folds the products with them) and part of the
 // Hessian is known to be zero. The eigen-decomposition of the remaining part gives the same clamped matrix.
+//
+// Edge (FRAME 3: a function of the length of r_1): with u along r_1 the 3 x 3 Hessian is diagonal, one value
+// along u and one across it: no rotations at all.
 //
 // Membrane (FRAME 2: an energy of the triangle's metric r_i . r_j): u along r_1, m in its plane, n its normal.
 // The second derivative of r_i . r_j couples equal axes only and its first derivative has no n part, so the
@@ -594,6 +601,44 @@ __device__ __forceinline__ void membrane_derivs(const double (&r)[6], const doub
     in.B[2] = helmert_entry<Term, T>(f.h, 1, 2, 1, 2);
 }
 
+template <class Term, typename T>
+__device__ __forceinline__ void edge_derivs(const double (&r)[3], const double* rest, const double* prm,
+                                            ElemOut<Term, T>& out, ClampIn<Term, T, 3>& in) {
+    const double rr = dot3(r, r), il = rr > 0.0 ? frsq(rr) : 0.0, l = length_of(rr, il);
+    T R[3][3];   // only the first axis matters: the derivatives across it vanish
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        in.u[c] = rr > 0.0 ? T(r[c] * il) : T(c == 0 ? 1 : 0);
+        R[c][0] = in.u[c];
+        R[c][1] = R[c][2] = T(0);
+    }
+    T h0, h1;
+    if constexpr (Term::NRES > 0) {
+        static_assert(Term::NRES == 1, "one residual per edge");
+        using S1 = D1<3, T>;
+        const S1 q[3] = {var<S1>(0, l), var<S1>(1, 0.0), var<S1>(2, 0.0)};
+        S1 res[1];
+        Term::template residual<S1>(q, rest, prm, res);
+        const T rv = T(res[0].v);
+        T g[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) g[c] = rv * res[0].g[c];
+        h0 = res[0].g[0] * res[0].g[0];
+        h1 = res[0].g[1] * res[0].g[1];
+        frame_gradient<Term, T>(0.5 * res[0].v * res[0].v, g, r, rest, prm, R, out);
+    } else {
+        using S = HD<3, T>;
+        const S q[3] = {var<S>(0, l), var<S>(1, 0.0), var<S>(2, 0.0)};
+        const S f = Term::template energy<S>(q, rest, prm);
+        h0 = f.h[Packed<3>::at(0, 0)];
+        h1 = f.h[Packed<3>::at(1, 1)];
+        frame_gradient<Term, T>(f.v, f.g, r, rest, prm, R, out);
+    }
+    constexpr double w = wmat(0, 0);
+    in.along = T(w * w) * h0;
+    in.across = T(w * w) * h1;
+}
+
 // blk (3 x 3 over the axes, the (i, j) block of a clamped matrix) turned back into the caller's axes
 template <class Term, typename T>
 __device__ __forceinline__ void rotate_block(const T (&B)[3][3], const T (&R)[3][3], int i, int j,
@@ -634,6 +679,9 @@ __device__ __forceinline__ void element_derivs(const double* xs, const double* r
         return;
     } else if constexpr (MODE == 3 && Term::FRAME == 2) {
         membrane_derivs<Term, T>(r, rest, prm, out, in);
+        return;
+    } else if constexpr (MODE == 3 && Term::FRAME == 3) {
+        edge_derivs<Term, T>(r, rest, prm, out, in);
         return;
     } else {
     using S = typename std::conditional<MODE == 1, D1<KR, T>, HD<KR, T>>::type;
@@ -781,6 +829,14 @@ __device__ __forceinline__ bool element_clamp(ClampIn<Term, T>& in, double eps, 
                 rotate_block<Term, T>(B, in.R, i, j, out);
             }
         return c4 && c2;
+    } else if constexpr (Term::FRAME == 3) {
+        const T a = in.along > te ? in.along : te, b = in.across > te ? in.across : te;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = i; j < 3; ++j)
+                out.hr[Packed<3>::at(i, j)] = (a - b) * in.u[i] * in.u[j] + (i == j ? b : T(0));
+        return true;
     } else {
         return clamp_matrix<Term::KR, T>(in.A, te, out.hr);
     }

@@ -46,7 +46,8 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
         ev = &p->prof_events[(size_t)p->prof_count++];
         MAD_HIP_TRY(hipEventRecord((*ev)[0], s));
     }
-    const bool fallback_pass = p->scatter == MAD_SCATTER_PATCH && p->prec == MAD_F32 && (mode & MAD_SPD);
+    const bool rows = p->by_rows();   // the patch scatter of light problems: the row-owned kernel
+    const bool fallback_pass = p->scatter == MAD_SCATTER_PATCH && !rows && p->prec == MAD_F32 && (mode & MAD_SPD);
     // the atomic and colored scatters add into zeroed outputs; the patch scatter writes every entry exactly once
     if (p->scatter != MAD_SCATTER_PATCH) {
         if (mode & MAD_GRAD) MAD_HIP_TRY(launch_fill(grad, m.nv * d, eb, s));
@@ -60,8 +61,8 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
     // Elsewhere several workgroups share a unit and the dispatcher is the queue: the counter's round trips to
     // memory, shared by all units, cost more than they gain (1024^2 shell FP32 1.37 -> 1.33 ms, 700 spheres
     // 2.76 -> 2.57, 1001^2 symmetric Dirichlet 225 -> 216 us, 200^2 Dirichlet FP64 26 -> 21 us).
-    const bool queue = p->scatter == MAD_SCATTER_PATCH &&
-                       (p->persistent == 2 || (p->persistent == 1 && p->prec == MAD_F64 && d == 3 && !p->light && kmode >= 2));
+    const bool queue = p->scatter == MAD_SCATTER_PATCH && !rows &&
+                       (p->persistent == 2 || (p->persistent == 1 && p->prec == MAD_F64 && d == 3 && kmode >= 2));
     // the FP64 redo queue's count and the patch queue's head, cleared by one small kernel
     MAD_HIP_TRY(launch_zero_counters(fallback_pass ? sc.fb_count : nullptr, queue ? sc.work_counter : nullptr, s));
     if (ev) MAD_HIP_TRY(hipEventRecord((*ev)[1], s));
@@ -87,7 +88,43 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
     if (ev) MAD_HIP_TRY(hipEventRecord((*ev)[2], s));
     const int np = p->patches.n;
     int n_partial_terms = (int)p->terms.size();
-    if (p->scatter == MAD_SCATTER_PATCH) {
+    if (rows) {
+        // Edge and vertex terms only: the row-owned kernel, which evaluates an edge from both of its rows and
+        // needs no accumulation between workgroups. FP32, clamped, against the patch kernel and its gather:
+        // 1000^2 cloth 322 -> 143 us, 250^2 41 -> 18 us, 50^2 23 -> 12 us; 1000^2 FP64 485 -> 240 us.
+        RowLaunch L{};
+        L.prec = p->prec;
+        L.mode = kmode;
+        L.want_grad = (mode & MAD_GRAD) ? 1 : 0;
+        L.hvp = hvp ? 1 : 0;
+        L.n_chunks = (int)p->n_row_chunks;
+        L.x = x;
+        L.v = v;
+        L.grad = grad;
+        L.hess = hess;
+        L.y = y;
+        L.rowptr = p->d_rowptr;
+        L.colidx = p->d_colidx;
+        L.edge = p->d_row_edge;
+        L.unit = reinterpret_cast<const int2*>(p->d_row_unit);
+        L.chunk_unit = p->d_chunk_unit;
+        L.partial = sc.partial;
+        L.flags = p->d_flags;
+        L.eps = p->opt.spd_eps;
+        for (size_t ti = 0; ti < p->terms.size(); ++ti) {
+            const Term& t = p->terms[ti];
+            RowTerm& A = t.ns == 2 ? L.edges[L.n_edge++] : L.verts[L.n_vert++];
+            A.kind = t.kind;
+            A.nrest = t.nrest;
+            A.n = t.n;
+            A.rest = t.d_jrest;
+            A.vdata = t.vdata;
+            std::memcpy(A.prm, t.prm, sizeof(A.prm));
+        }
+        MAD_HIP_TRY(launch_eval_rows(L, s));
+        if (ev)
+            for (size_t k = 3; k < ev->size() - 1; ++k) MAD_HIP_TRY(hipEventRecord((*ev)[k], s));
+    } else if (p->scatter == MAD_SCATTER_PATCH) {
         PatchLaunch L{};
         L.prec = p->prec;
         L.mode = kmode;
@@ -125,7 +162,6 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
         L.n_cu = p->n_cu;
         L.normals = sc.normals;
         L.shell = p->shell ? 1 : 0;
-        L.light = p->light ? 1 : 0;
         L.hvp = hvp ? 1 : 0;
         L.v = v;
         L.y = y;
@@ -275,6 +311,9 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
         const int ncomp = (int)m.comp_off.size() - 1;
         if (p->scatter == MAD_SCATTER_COLOR)
             MAD_HIP_TRY(launch_energy_reduce(sc.partial, 1, (int)p->n_color_slots, p->d_color_comp_ptr,
+                                             std::max(ncomp, 1), m.batched, energy, sc.comp_energy, s));
+        else if (rows)
+            MAD_HIP_TRY(launch_energy_reduce(sc.partial, 1, (int)p->n_row_chunks, p->d_row_comp_ptr,
                                              std::max(ncomp, 1), m.batched, energy, sc.comp_energy, s));
         else
             MAD_HIP_TRY(launch_energy_reduce(sc.partial, n_partial_terms, np, p->d_comp_patch_ptr,

@@ -201,6 +201,36 @@ void unit_segments(const Term& t, int32_t np, int64_t nv, std::vector<uint8_t>& 
     for (auto& th : pool) th.join();
 }
 
+// Units and chunks of the row-owned evaluation. A chunk holds a multiple of `step` units (one for each wave) of
+// one component, four times that where the mesh still gives `wanted` chunks, so that a wave has further units
+// whose loads it can start on.
+void row_units(const std::vector<int32_t>& rowptr, const std::vector<int64_t>& comp_off, int step, int64_t wanted,
+               std::vector<int32_t>& unit_row, std::vector<int32_t>& chunk_unit, std::vector<int32_t>& comp_chunk) {
+    const int64_t nv = (int64_t)rowptr.size() - 1, ncomp = std::max<int64_t>((int64_t)comp_off.size() - 1, 1);
+    auto comp_end = [&](int64_t c) { return comp_off.size() > 1 ? comp_off[(size_t)c + 1] : nv; };
+    unit_row.clear();
+    std::vector<int32_t> comp_unit(1, 0);
+    int64_t r = 0;
+    for (int64_t c = 0; c < ncomp; ++c) {
+        while (r < comp_end(c)) {
+            const int64_t b = r++;
+            while (r < comp_end(c) && rowptr[r + 1] - rowptr[b] <= 64) ++r;
+            unit_row.push_back((int32_t)b);
+        }
+        comp_unit.push_back((int32_t)unit_row.size());
+    }
+    const int64_t nu = (int64_t)unit_row.size();
+    unit_row.push_back((int32_t)nv);
+    const int32_t per = (int32_t)(step * std::min<int64_t>(4, std::max<int64_t>(1, nu / (step * std::max<int64_t>(wanted, 1)))));
+    chunk_unit.clear();
+    comp_chunk.assign(1, 0);
+    for (int64_t c = 0; c < ncomp; ++c) {
+        for (int32_t u = comp_unit[c]; u < comp_unit[c + 1]; u += per) chunk_unit.push_back(u);
+        comp_chunk.push_back((int32_t)chunk_unit.size());
+    }
+    chunk_unit.push_back((int32_t)nu);
+}
+
 // Colored scatter (the coloring alternative of Sec. 5.5). Each term's elements are colored greedily in
 // their current (patch) order: an element takes the lowest color that no earlier element sharing one of its
 // vertices holds (per-vertex bit sets of used colors, widened when a color beyond them is needed), so no two

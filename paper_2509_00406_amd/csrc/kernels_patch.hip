@@ -398,13 +398,13 @@ __device__ __forceinline__ void eval_patch_one(const PatchLaunch& L, int p, unsi
                 patch_term<TermInertia, T, MODE>(L, A, t, p, e0, last, sx, sg, sh, sy, lock, esum, bad);
                 break;
             case K_STVK:
-                if constexpr (FAM != 2) patch_term<TermStVK, T, MODE>(L, A, t, p, e0, last, sx, sg, sh, sy, lock, esum, bad);
+                patch_term<TermStVK, T, MODE>(L, A, t, p, e0, last, sx, sg, sh, sy, lock, esum, bad);
                 break;
             case K_BENDING:
-                if constexpr (FAM != 2) patch_term<TermBending, T, MODE>(L, A, t, p, e0, last, sx, sg, sh, sy, lock, esum, bad);
+                patch_term<TermBending, T, MODE>(L, A, t, p, e0, last, sx, sg, sh, sy, lock, esum, bad);
                 break;
             case K_TRI_AREA:
-                if constexpr (FAM != 2) patch_term<TermTriArea, T, MODE>(L, A, t, p, e0, last, sx, sg, sh, sy, lock, esum, bad);
+                patch_term<TermTriArea, T, MODE>(L, A, t, p, e0, last, sx, sg, sh, sy, lock, esum, bad);
                 break;
             case K_SHELL_TRI:
                 if constexpr (FAM == 1) patch_term<TermShellTri, T, MODE>(L, A, t, p, e0, last, sx, sg, sh, sy, lock, esum, bad);
@@ -513,20 +513,15 @@ __device__ __forceinline__ void eval_patch_body(const PatchLaunch& L) {
 
 // FAM: the term family compiled into an instantiation. 0: the catalogue; 1: the catalogue and the
 // shell-feature terms (analytic and learned per-triangle densities), whose register needs would
-// otherwise burden the catalogue's kernel; 2: light terms only (edge, spring, vertex and residual
-// terms: 3 x 3 reduced Hessians), held to fewer registers for more waves per SIMD, since such
-// elements wait on memory more than they compute.
-// FP32 families 0 and 1: the compiler is held to 256 registers so two waves share each SIMD (the
-// second wave hides the latency of the long dependent rotation chains).
+// otherwise burden the catalogue's kernel. (Problems of edge and vertex terms only are evaluated by rows,
+// kernels_rows.hip.)
+// FP32: the compiler is held to 256 registers so two waves share each SIMD (the second wave hides the latency
+// of the long dependent rotation chains).
 // BLK: threads per workgroup (the tile): 256 (four waves; two workgroups share a CU) or, for FP32, 512
-// (eight waves; one workgroup holds the CU's LDS for larger patches, or two light workgroups share it).
+// (eight waves; one workgroup holds the CU's LDS for larger patches).
 template <int MODE, int D, int FAM, int BLK>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2))) void k_eval_patch_f32(PatchLaunch L) {
     eval_patch_body<float, MODE, D, FAM, BLK>(L);
-}
-template <int MODE, int D, int BLK>
-__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_patch_light_f32(PatchLaunch L) {
-    eval_patch_body<float, MODE, D, 2, BLK>(L);
 }
 template <int MODE, int D, int FAM>
 __global__ __launch_bounds__(kBlock) void k_eval_patch_f64(PatchLaunch L) {
@@ -740,13 +735,8 @@ static int persistent_grid(K kernel, const PatchLaunch& L, int blk) {
 template <int MODE, int D, int FAM, int BLK>
 static void launch_patch_f32(const PatchLaunch& L, hipStream_t s) {
     const dim3 block(BLK);
-    if constexpr (FAM == 2) {
-        const dim3 grid(L.persistent ? persistent_grid(k_eval_patch_light_f32<MODE, D, BLK>, L, BLK) : L.n_patch);
-        hipLaunchKernelGGL((k_eval_patch_light_f32<MODE, D, BLK>), grid, block, L.lds_bytes, s, L);
-    } else {
-        const dim3 grid(L.persistent ? persistent_grid(k_eval_patch_f32<MODE, D, FAM, BLK>, L, BLK) : L.n_patch);
-        hipLaunchKernelGGL((k_eval_patch_f32<MODE, D, FAM, BLK>), grid, block, L.lds_bytes, s, L);
-    }
+    const dim3 grid(L.persistent ? persistent_grid(k_eval_patch_f32<MODE, D, FAM, BLK>, L, BLK) : L.n_patch);
+    hipLaunchKernelGGL((k_eval_patch_f32<MODE, D, FAM, BLK>), grid, block, L.lds_bytes, s, L);
 }
 
 template <int MODE, int D, int FAM>
@@ -765,10 +755,6 @@ static void launch_patch_kernel(bool f32, const PatchLaunch& L, hipStream_t s) {
     if constexpr (D == 3) {
         if (L.shell) {
             launch_patch_variant<MODE, D, 1>(f32, L, s);
-            return;
-        }
-        if (L.light) {
-            launch_patch_variant<MODE, D, 2>(f32, L, s);
             return;
         }
     }

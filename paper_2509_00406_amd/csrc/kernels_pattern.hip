@@ -571,10 +571,15 @@ int insert_pairs_device(mad_problem* p, const int32_t* pairs, int64_t n, int64_t
     MAD_HIP_TRY(remap(p->d_gb_gidx, p->n_gb));
     MAD_HIP_TRY(remap(p->d_gb_gidxT, p->n_gb));
     MAD_HIP_TRY(remap(p->d_orphan_block, p->n_orphan_block));
+    if (p->d_row_edge) {
+        MAD_HIP_TRY(launch_move_edges(p->d_row_edge, p->nnzb, B.map, p->d_row_edge_b, total, s));
+        MAD_HIP_TRY(launch_unit_blocks(p->d_rowptr_b, p->d_row_unit, p->n_row_units + 1, s));
+    }
     for (auto& t : p->terms) MAD_HIP_TRY(remap(t.d_slots, t.d_slots ? t.n * t.ns * t.ns : 0));
     MAD_HIP_TRY(hipStreamSynchronize(s));
     std::swap(p->d_rowptr, p->d_rowptr_b);
     std::swap(p->d_colidx, p->d_colidx_b);
+    if (p->d_row_edge) std::swap(p->d_row_edge, p->d_row_edge_b);
     p->nnzb = total;
     p->n_extra += added;
     p->host_pattern_stale = true;

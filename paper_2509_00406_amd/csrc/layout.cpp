@@ -45,6 +45,8 @@ static void free_layout(mad_problem* p) {
         t.d_slot_map = nullptr;
     }
     p->d_color_comp_ptr = nullptr;
+    p->d_row_edge = p->d_row_edge_b = p->d_row_unit = p->d_chunk_unit = p->d_row_comp_ptr = nullptr;
+    p->n_row_chunks = p->n_row_units = 0;
     p->d_lv_ptr = p->d_lv_global = p->d_lv_halo = nullptr;
     p->d_lb_ptr = p->d_lb_gidx = p->d_lb_gidxT = p->d_lb_halo = nullptr;
     p->n_lb = 0;
@@ -75,7 +77,7 @@ int default_patch_faces(int64_t n_faces, int n_cu, bool light) {
 }
 
 size_t lds_budget(const mad_problem* p) {
-    return (p->wg_waves == 8 && p->prec == MAD_F32 && !p->light) ? kLdsBudgetWide : kLdsBudget;
+    return (p->wg_waves == 8 && p->prec == MAD_F32) ? kLdsBudgetWide : kLdsBudget;
 }
 
 // Build the patches and the element order (host), then upload the element arrays. If the pattern
@@ -90,7 +92,7 @@ int build_layout(mad_problem* p, int target, int scatter, int persistent, hipStr
     // the fit below needs only which elements each patch holds: the colour order comes after it
     build_patches(m, target, p->patches);
     order_terms(p);
-    if (scatter == MAD_SCATTER_PATCH) {
+    if (scatter == MAD_SCATTER_PATCH && !p->light) {
         // Every patch has to fit the LDS budget and have at most kMaxPatchUnits work units. Where more than
         // one in 32 does not, the patch target shrinks by what most of them are over; the few are halved, which
         // keeps the others large.
@@ -123,7 +125,8 @@ int build_layout(mad_problem* p, int target, int scatter, int persistent, hipStr
             order_terms(p);
         }
     }
-    for (auto& t : p->terms) color_within_patches(t, m.nv);
+    if (!p->by_rows())
+        for (auto& t : p->terms) color_within_patches(t, m.nv);
     std::vector<int32_t> comp_slot_ptr;
     p->n_color_slots = 0;
     if (scatter == MAD_SCATTER_COLOR) color_order(p, comp_slot_ptr);
@@ -142,9 +145,9 @@ int build_layout(mad_problem* p, int target, int scatter, int persistent, hipStr
         if ((rc = upload_layout(p, (void**)&t.d_rest, rs.data(), rs.size() * 8, s)) != MAD_OK) return rc;
         if ((rc = upload_layout(p, (void**)&t.d_elem_ptr, t.elem_ptr.data(), t.elem_ptr.size() * 4, s)) != MAD_OK)
             return rc;
-        if (kind_nres(t.kind) > 0) {
+        if (kind_nres(t.kind) > 0 || p->by_rows()) {
             // the Jacobian kernel runs in element order, so that each element's rows are written next to its
-            // neighbours' (the evaluation kernels run in patch order)
+            // neighbours' (the patch kernels run in patch order); the row kernel finds an edge by its number
             std::vector<double> rj((size_t)t.n * t.nrest);
             for (int64_t e = 0; e < t.n; ++e)
                 for (int k = 0; k < t.nrest; ++k) rj[(int64_t)k * t.n + e] = t.rest[(int64_t)e * t.nrest + k];
@@ -213,6 +216,36 @@ int build_scatter(mad_problem* p, hipStream_t s) {
         p->host_pattern_stale = false;
     }
     p->n_extra = 0;
+    if (p->by_rows()) {
+        std::vector<int32_t> unit_row, chunk_unit, comp_chunk;
+        row_units(p->h_rowptr, p->mesh->comp_off, 4, 8ll * std::max(p->n_cu, 1), unit_row, chunk_unit, comp_chunk);
+        p->n_row_chunks = (int64_t)chunk_unit.size() - 1;
+        p->n_row_units = (int64_t)unit_row.size() - 1;
+        std::vector<int32_t> unit;
+        for (int32_t r : unit_row) {
+            unit.push_back(r);
+            unit.push_back(p->h_rowptr[(size_t)r]);
+        }
+        if ((rc = upload_layout(p, (void**)&p->d_row_unit, unit.data(), unit.size() * 4, s)) != MAD_OK ||
+            (rc = upload_layout(p, (void**)&p->d_chunk_unit, chunk_unit.data(), chunk_unit.size() * 4, s)) != MAD_OK ||
+            (rc = upload_layout(p, (void**)&p->d_row_comp_ptr, comp_chunk.data(), comp_chunk.size() * 4, s)) != MAD_OK)
+            return rc;
+        const size_t cap = (size_t)std::max<int64_t>({p->nnzb, p->nnzb_cap, 1});
+        if ((rc = alloc_layout(p, (void**)&p->d_row_edge, sizeof(int32_t) * cap)) != MAD_OK) return rc;
+        if (p->pair_reserve > 0 && (rc = alloc_layout(p, (void**)&p->d_row_edge_b, sizeof(int32_t) * cap)) != MAD_OK)
+            return rc;
+        int32_t* d_edges = nullptr;
+        const std::vector<int32_t>& edges = p->mesh->edges;
+        if ((rc = upload_layout(p, (void**)&d_edges, edges.data(), edges.size() * 4, s)) != MAD_OK) return rc;
+        const bool any = std::any_of(p->terms.begin(), p->terms.end(), [](const Term& t) { return t.ns == 2; });
+        MAD_HIP_TRY(launch_block_edges(d_edges, any ? p->mesh->ne() : 0, p->d_rowptr, p->d_colidx, p->nnzb,
+                                       p->d_row_edge, p->d_flags, s));
+        if ((rc = alloc_layout(p, (void**)&p->d_partial,
+                               sizeof(double) * (size_t)std::max<int64_t>(p->n_row_chunks, 1))) != MAD_OK)
+            return rc;
+        MAD_HIP_TRY(hipStreamSynchronize(s));
+        return MAD_OK;
+    }
     if (p->scatter != MAD_SCATTER_PATCH) {   // atomic and colored: the global block of every element pair
         for (auto& t : p->terms) {
             if ((rc = alloc_layout(p, (void**)&t.d_slots, sizeof(int32_t) * std::max<int64_t>(1, t.n * t.ns * t.ns))) !=

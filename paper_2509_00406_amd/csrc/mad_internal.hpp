@@ -143,6 +143,15 @@ struct mad_problem {
     std::string tune_report;              // last autotune table (JSON)
     bool shell = false;                   // a term reads the shell features (needs vertex normals)
     bool light = true;                    // every term is a spring, inertia, edge-length or residual term
+    // row-owned evaluation (light problems with the patch scatter): units of rows, a workgroup's chunk of them
+    int32_t* d_row_edge = nullptr;        // [nnzb capacity] edge of each block
+    int32_t* d_row_edge_b = nullptr;      // the second buffer of an insertion
+    int32_t* d_row_unit = nullptr;        // [units + 1][2] first row, first block
+    int64_t n_row_units = 0;
+    int32_t* d_chunk_unit = nullptr;
+    int32_t* d_row_comp_ptr = nullptr;    // [n_comp + 1] chunks of each component
+    int64_t n_row_chunks = 0;
+    bool by_rows() const { return light && scatter == MAD_SCATTER_PATCH; }
     int32_t* d_tris = nullptr;            // [nt][3] mesh triangles (normals)
     int32_t* d_vf_ptr = nullptr;          // [nv + 1] vertex -> triangles, ascending
     int32_t* d_vf = nullptr;
@@ -221,6 +230,9 @@ void color_within_patches(Term& t, int64_t nv);
 // each (may be NULL): those of every patch
 void patch_extent(const mad_problem* p, int32_t* max_lv, int32_t* max_lb,
                   std::vector<std::pair<int32_t, int32_t>>* each = nullptr);
+// units of consecutive rows with at most 64 blocks (or one row), chunks of units inside one component
+void row_units(const std::vector<int32_t>& rowptr, const std::vector<int64_t>& comp_off, int step, int64_t wanted,
+               std::vector<int32_t>& unit_row, std::vector<int32_t>& chunk_unit, std::vector<int32_t>& comp_chunk);
 void unit_segments(const Term& t, int32_t np, int64_t nv, std::vector<uint8_t>& seg);
 // colored scatter: greedy coloring of each term's elements (no shared vertex within a color), elements
 // sorted by color then component, chunks, energy slots; comp_slot_ptr [n_comp + 1] (host)
@@ -336,7 +348,6 @@ struct PatchLaunch {
     double eps, qmin;
     const double* normals;  // [nv][3] unit vertex normals (shell-feature terms)
     int shell;              // the problem has shell-feature terms (selects the kernel variant)
-    int light;              // every term is a light term (edge, spring, vertex, residual): the light variant
     int term_order[8];      // terms by decreasing element cost (work units of the costliest first)
     int hvp;                // matrix-free mode: y = H v instead of assembling H (modes 2, 3)
     const double* v;        // [nv][D]
@@ -351,6 +362,40 @@ struct PatchLaunch {
     PatchTermArgs terms[8];
 };
 hipError_t launch_eval_patch(const PatchLaunch& L, hipStream_t s);
+
+// row-owned evaluation of light problems (kernels_rows.hip)
+struct RowTerm {
+    int kind, nrest;
+    int64_t n;
+    const double* rest;      // SoA [nrest][n], element order
+    const double* vdata;     // [nv][NVD] caller's per-vertex data (vertex terms)
+    double prm[4];
+};
+struct RowLaunch {
+    int prec, mode, want_grad, hvp, n_edge, n_vert, n_chunks;
+    const double* x;
+    const double* v;         // matrix-free mode: y = H v
+    void* grad;
+    void* hess;
+    void* y;
+    const int32_t* rowptr;
+    const int32_t* colidx;
+    const int32_t* edge;       // [nnzb] edge of an off-diagonal block, -1 for the others
+    const int2* unit;          // [units + 1] first row and first block of each unit
+    const int32_t* chunk_unit; // [chunks + 1] first unit of each workgroup's chunk
+    double* partial;           // [chunks]
+    int32_t* flags;
+    double eps;
+    RowTerm edges[8], verts[8];
+};
+hipError_t launch_eval_rows(const RowLaunch& L, hipStream_t s);
+// the edge of every block; after an insertion (old block i is now block map[i]), its new place
+hipError_t launch_block_edges(const int32_t* edges, int64_t n_edges, const int32_t* rowptr, const int32_t* colidx,
+                              int64_t nnzb, int32_t* edge, int32_t* flags, hipStream_t s);
+// the first block of every unit from its first row
+hipError_t launch_unit_blocks(const int32_t* rowptr, int32_t* unit, int64_t n_entries, hipStream_t s);
+hipError_t launch_move_edges(const int32_t* from, int64_t n, const int32_t* map, int32_t* to, int64_t n_to,
+                             hipStream_t s);
 
 // sum the halo partials of every shared entry in a fixed order and write it once; zero orphans
 struct GatherLaunch {

@@ -11,7 +11,8 @@
 // false: the per-vertex inertia) seeds its stencil DOFs themselves, KR = NS*D.
 // NVD: values the term reads per stencil vertex from a caller-owned vertex array.
 // FRAME: structure of the Hessian in a frame of the current element, used by the clamp (element.hpp): 1 a hinge
-// (a function of the dihedral angle alone), 2 a membrane (a function of the triangle's metric r_i . r_j), 0 none.
+// (a function of the dihedral angle alone), 2 a membrane (a function of the triangle's metric r_i . r_j), 3 an
+// edge (a function of its length), 0 none.
 #pragma once
 #include "dual.hpp"
 
@@ -37,7 +38,7 @@ template <typename S> __device__ __forceinline__ S dot(const V3<S>& a, const V3<
 // Listing 1: squared edge length. r = x1 - x0.
 struct TermEdgeSqlen {
     static constexpr int NS = 2, D = 3, KR = 3, NREST = 0, NAUX = 0, NPSI = 0, NVD = 0, NRES = 0;
-    static constexpr int FRAME = 0;
+    static constexpr int FRAME = 3;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double*, const double*) {
         return r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
@@ -48,7 +49,7 @@ struct TermEdgeSqlen {
 // l the rest length. rest = {l^2, 1 / l^2}, params = {k, w}.
 struct TermSpring {
     static constexpr int NS = 2, D = 3, KR = 3, NREST = 2, NAUX = 0, NPSI = 0, NVD = 0, NRES = 0;
-    static constexpr int FRAME = 0;
+    static constexpr int FRAME = 3;
     static constexpr bool TI = true;
     template <typename S> __device__ static S energy(const S* r, const double* rest, const double* prm) {
         const S q = (r[0] * r[0] + r[1] * r[1] + r[2] * r[2]) * rest[1] + (-1.0);
@@ -96,7 +97,7 @@ struct TermResPosition {
 // Edge-length residual (a least-squares spring): r = sqrt(k) (|x1 - x0| - l), rest = {l}, params = {k}.
 struct TermResEdge {
     static constexpr int NS = 2, D = 3, KR = 3, NREST = 1, NAUX = 0, NPSI = 0, NVD = 0, NRES = 1;
-    static constexpr int FRAME = 0;
+    static constexpr int FRAME = 3;
     static constexpr bool TI = true;
     template <typename S> __device__ static void residual(const S* r, const double* rest, const double* prm, S* out) {
         out[0] = (dsqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]) + (-rest[0])) * sqrt(prm[0]);
