@@ -188,20 +188,21 @@ __device__ __forceinline__ double least_normal(double) { return 2.22507385850720
 // problems on multiprocessor arrays" (SIAM J. Sci. Stat. Comput., 1985). Rotations
 // in one round touch disjoint (p, q) planes, so their parameters depend only on entries no other
 // rotation of the round changes: they are computed together, giving independent instruction
-// streams. The rotation zeroing a_pq uses t = tan(phi) = a_pq / (h + sgn(h) sqrt(h^2 + a_pq^2)),
-// h = (a_qq - a_pp) / 2 (the smaller root of t^2 + 2 t h / a_pq - 1 = 0), c = 1/sqrt(1 + t^2),
+// streams. The rotation zeroing a_pq uses t = tan(phi) = 2 a_pq / (h + sgn(h) sqrt(h^2 + 4 a_pq^2)),
+// h = a_qq - a_pp (the smaller root of t^2 + t h / a_pq - 1 = 0), c = 1/sqrt(1 + t^2),
 // s = t c, and A <- J^T A J, V <- V J with J_pp = J_qq = c, J_pq = s, J_qp = -s.
 //
 // Scaled rotations (the idea of the fast Givens transformation of W. M. Gentleman, 1973, and
 // S. Hammarling, 1974, applied to Jacobi rotations): the off-diagonal entries and the eigenvector
-// columns are kept with a diagonal scale, a_ij = d_i d_j b_ij (i != j) and V = W diag(d), while the diagonal of A is kept as is. A
-// rotation in the (p, q) plane multiplies d_p and d_q by c; the stored entries then change by one
-// fused multiply-add each, b_ip -= t (d_q / d_p) b_iq and b_iq += t (d_p / d_q) b_ip (the same for
-// W's columns), where the plain rotation needs two products and a multiply-add. The reciprocals
-// e = 1/d are carried along (e <- e sqrt(1 + t^2)), so no division is needed. c >= 1/sqrt(2), so
-// after s sweeps d >= 2^(-s (N - 1) / 2): no underflow in FP32 within the sweep limit, and the
+// columns are kept with a diagonal scale, 2 a_ij = d_i d_j b_ij (i != j) and V = W diag(d) / sqrt(2), while the
+// diagonal of A is kept as is. A rotation in the (p, q) plane multiplies d_p and d_q by c; the stored entries then
+// change by one fused multiply-add each, b_ip -= t (d_q / d_p) b_iq and b_iq += t (d_p / d_q) b_ip (the same for
+// W's columns), where the plain rotation needs two products and a multiply-add. With e = 1/d^2 carried along
+// (e <- e (1 + t^2)) the two factors are t d_p d_q times e_p and e_q, so no division is needed; the sqrt(2)
+// that d starts with makes d_p d_q b_pq = 2 a_pq, which is what t and the diagonal take. c >= 1/sqrt(2), so
+// after s sweeps d >= 2^(1/2 - s (N - 1) / 2): no underflow in FP32 within the sweep limit, and the
 // stored entries grow by at most the inverse.
-// On return A's diagonal holds the eigenvalues and W diag(d) the eigenvectors. The matrix is
+// On return A's diagonal holds the eigenvalues and W diag(d) / sqrt(2) the eigenvectors. The matrix is
 // scaled to max |a_ij| = 1 first (and the eigenvalues scaled back) so squares cannot overflow.
 // Returns whether the off-diagonal mass fell below tol of the Frobenius norm within max_sweeps.
 __host__ __device__ constexpr int rr_players(int n) { return n + (n & 1); }
@@ -218,11 +219,11 @@ __device__ __forceinline__ bool jacobi_converged(const T (&A)[Packed<N>::N], con
         dg += A[Packed<N>::at(p, p)] * A[Packed<N>::at(p, p)];
 #pragma unroll
         for (int q = p + 1; q < N; ++q) {
-            const T a = dsc[p] * dsc[q] * A[Packed<N>::at(p, q)];
+            const T a = dsc[p] * dsc[q] * A[Packed<N>::at(p, q)];   // twice the entry
             off += a * a;
         }
     }
-    return off <= tol * tol * (dg + T(2) * off);
+    return off <= tol * tol * (T(4) * dg + T(2) * off);
 }
 
 // one sweep: every pair once, round by round
@@ -231,32 +232,33 @@ __device__ __forceinline__ void jacobi_sweep(T (&A)[Packed<N>::N], T (&W)[N][N],
     constexpr int M = rr_players(N), H = M / 2;
 #pragma unroll
     for (int r = 0; r < M - 1; ++r) {
-        T tn[H], ta[H];
+        T tn[H], ta[H], ts[H];
         // parameters of the round's rotations (independent of each other)
 #pragma unroll
         for (int k = 0; k < H; ++k) {
             const int a = rr_a(M, r, k), b = rr_b(M, r, k);
             if (a >= N || b >= N) continue;
             const int p = a < b ? a : b, q = a < b ? b : a;
-            const T apq = dsc[p] * dsc[q] * A[Packed<N>::at(p, q)];
-            const T h = T(0.5) * A[Packed<N>::at(q, q)] - T(0.5) * A[Packed<N>::at(p, p)];
-            // the floor keeps t finite (and 0 for a_pq = 0) where h^2 + a_pq^2 underflows
-            const T root = fsqrt(fmax(h * h + apq * apq, least_normal(h)));
-            const T t = apq * frcp(h + copysign(root, h));
+            const T dd = dsc[p] * dsc[q];
+            const T a2 = dd * A[Packed<N>::at(p, q)];   // 2 a_pq
+            const T h2 = A[Packed<N>::at(q, q)] - A[Packed<N>::at(p, p)];
+            // the least normal number keeps t finite (and 0 for a_pq = 0) where the squares underflow
+            const T root = fsqrt(h2 * h2 + (a2 * a2 + least_normal(a2)));
+            const T t = a2 * frcp(h2 + copysign(root, h2));
             tn[k] = t;
-            ta[k] = t * apq;
+            ta[k] = t * a2;
+            ts[k] = t * dd;
         }
 #pragma unroll
         for (int k = 0; k < H; ++k) {
             const int a = rr_a(M, r, k), b = rr_b(M, r, k);
             if (a >= N || b >= N) continue;
             const int p = a < b ? a : b, q = a < b ? b : a;
-            const T t = tn[k];
-            const T w = t * t + T(1);
+            const T w = tn[k] * tn[k] + T(1);
             const T c = frsq(w);
-            const T u = t * dsc[q] * inv[p], v = t * dsc[p] * inv[q];
-            A[Packed<N>::at(p, p)] -= ta[k];
-            A[Packed<N>::at(q, q)] += ta[k];
+            const T u = ts[k] * inv[p], v = ts[k] * inv[q];
+            A[Packed<N>::at(p, p)] -= T(0.5) * ta[k];
+            A[Packed<N>::at(q, q)] += T(0.5) * ta[k];
             A[Packed<N>::at(p, q)] = T(0);
 #pragma unroll
             for (int i = 0; i < N; ++i) {
@@ -271,11 +273,10 @@ __device__ __forceinline__ void jacobi_sweep(T (&A)[Packed<N>::N], T (&W)[N][N],
                 W[i][p] = g - u * h;
                 W[i][q] = h + v * g;
             }
-            const T ic = w * c;
             dsc[p] *= c;
             dsc[q] *= c;
-            inv[p] *= ic;
-            inv[q] *= ic;
+            inv[p] *= w;
+            inv[q] *= w;
         }
     }
 }
@@ -285,8 +286,8 @@ __device__ __forceinline__ bool jacobi_eig(T (&A)[Packed<N>::N], T (&W)[N][N], T
     T inv[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        dsc[i] = T(1);
-        inv[i] = T(1);
+        dsc[i] = T(1.4142135623730951);
+        inv[i] = T(0.5);
 #pragma unroll
         for (int j = 0; j < N; ++j) W[i][j] = (i == j) ? T(1) : T(0);
     }
@@ -751,7 +752,7 @@ __device__ __forceinline__ void element_derivs(const double* xs, const double* r
     }
 }
 
-// C = U diag(max(lambda, floor)) U^T (U = V diag(dsc)) of the symmetric N x N matrix A; returns whether the
+// C = U diag(max(lambda, floor)) U^T (U = V diag(dsc) / sqrt(2)) of the symmetric N x N matrix A; returns whether the
 // eigen-decomposition converged
 template <int N, typename T>
 __device__ __forceinline__ bool clamp_matrix(T (&A)[Packed<N>::N], T te, T (&C)[Packed<N>::N]) {
@@ -761,9 +762,9 @@ __device__ __forceinline__ bool clamp_matrix(T (&A)[Packed<N>::N], T te, T (&C)[
     for (int i = 0; i < Packed<N>::N; ++i) C[i] = T(0);
 #pragma unroll
     for (int m = 0; m < N; ++m) {
-        // eigenvector m is column m of V times dsc[m]: its scale squared goes with the eigenvalue
+        // eigenvector m is column m of V times dsc[m] / sqrt(2): its scale squared goes with the eigenvalue
         const T lam = A[Packed<N>::at(m, m)];
-        const T lp = (lam > te ? lam : te) * (dsc[m] * dsc[m]);
+        const T lp = (lam > te ? lam : te) * (T(0.5) * dsc[m] * dsc[m]);
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const T li = lp * V[i][m];
