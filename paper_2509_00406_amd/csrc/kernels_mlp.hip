@@ -433,12 +433,15 @@ hipError_t launch_mlp_head(const MlpHeadLaunch& L, hipStream_t s) {
 }
 
 // ---- training ------------------------------------------------------------------------------------
-// One wave per sample at a time, lane m = hidden unit m. Forward mode carries the six tangents
+// One wave per sample, lane m = hidden unit m. Forward mode carries the six tangents
 // d/dxh (xh = s_in * z) through both layers; reverse mode then differentiates
 //   loss = (psi - W)^2 / (c_e B) + lam_g sum_i (dpsi/dz_i - dW_i)^2 / (c_g[i] B)   (B = batch size)
-// with respect to every parameter. Each wave accumulates its samples' gradients in registers and
-// writes one partial row; the rows are summed in a fixed order afterwards.
-constexpr int kTrainBlock = 256;
+// with respect to every parameter. A workgroup takes four samples at a time; the gradient of W2, the sum of the
+// samples' outer products, is shared out over its waves (16 columns each, summed over the four samples), so that a
+// lane holds 16 of its sums and not 64 (which spilled). Each workgroup writes one partial row; the rows are summed
+// in a fixed order afterwards. A minibatch of 512 is one sample per wave over 128 workgroups and bound by the
+// latency of that sample's chain: 19 us, 132 us with eight samples after one another on each of 64 waves.
+constexpr int kTrainWaves = 4, kTrainBlock = 64 * kTrainWaves;
 constexpr int kW2Pad = kHid + 1;   // padded LDS rows: lane m reading row m is bank-conflict free
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -449,29 +452,28 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 __global__ __launch_bounds__(kTrainBlock) void k_mlp_train(MlpTrainLaunch L) {
     __shared__ float sW2[kHid * kW2Pad];
-    __shared__ float sX[kTrainBlock / 64][kHid][8];    // per wave: h1, T1 (6), pad
-    __shared__ float sD[kTrainBlock / 64][kHid][8];    // per wave: delta2, G2a (6), pad
+    __shared__ __align__(16) float sX[kTrainWaves][kHid][8];    // per wave: h1, T1 (6), pad
+    __shared__ __align__(16) float sD[kTrainWaves][kHid][8];    // per wave: delta2, G2a (6), pad
+    constexpr int kCols = kHid / kTrainWaves;   // columns of W2 whose gradient a wave sums
     for (int i = threadIdx.x; i < kHid * kHid; i += blockDim.x)
         sW2[(i / kHid) * kW2Pad + i % kHid] = L.params[kOffW2 + i];
-    __syncthreads();
     const int m = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int gw = blockIdx.x * (blockDim.x >> 6) + wv;   // global wave
     float w1[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) w1[i] = L.params[kOffW1 + m * 6 + i];
     const float b1 = L.params[kOffB1 + m], b2 = L.params[kOffB2 + m], w3 = L.params[kOffW3 + m];
     const float b3 = L.params[kOffB3];
-    float gW2[kHid];
+    float gW2[kCols];
 #pragma unroll
-    for (int k = 0; k < kHid; ++k) gW2[k] = 0.0f;
+    for (int k = 0; k < kCols; ++k) gW2[k] = 0.0f;
     float gW1[6] = {0, 0, 0, 0, 0, 0};
     float gb1 = 0.0f, gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, loss = 0.0f;
     const float inv_b = 1.0f / float(L.count);
     // every wave runs the same number of rounds (the block barriers below need it); a wave past the
     // end of the batch evaluates sample 0 of the batch with zero weight
-    const int64_t rounds = (L.count + L.n_waves - 1) / L.n_waves;
-    for (int64_t it = 0; it < rounds; ++it) {
-        const int64_t q = gw + it * L.n_waves;
+    const int64_t per_round = (int64_t)L.n_rows * kTrainWaves;
+    for (int64_t q0 = 0; q0 < L.count; q0 += per_round) {
+        const int64_t q = q0 + (int64_t)blockIdx.x * kTrainWaves + wv;
         const bool active = q < L.count;
         const int64_t qi = active ? q : 0;
         const int64_t smp = L.idx ? (int64_t)L.idx[L.base + qi] : L.base + qi;
@@ -488,17 +490,23 @@ __global__ __launch_bounds__(kTrainBlock) void k_mlp_train(MlpTrainLaunch L) {
 #pragma unroll
         for (int i = 0; i < 6; ++i) a1 = fmaf(w1[i], xh[i], a1);
         const float h1 = softplusf(a1), d1 = logisticf(a1), d1p = d1 * (1.0f - d1);
-        sX[wv][m][0] = h1;
-#pragma unroll
-        for (int i = 0; i < 6; ++i) sX[wv][m][1 + i] = d1 * w1[i];
-        __syncthreads();
+        float4* x4 = reinterpret_cast<float4*>(sX[wv][m]);
+        x4[0] = make_float4(h1, d1 * w1[0], d1 * w1[1], d1 * w1[2]);
+        x4[1] = make_float4(d1 * w1[3], d1 * w1[4], d1 * w1[5], 0.0f);
+        __syncthreads();   // the first round's W2 as well
         // layer 2 (unit m): a2 = W2[m, :] h1 + b2, T2a[m, i] = W2[m, :] T1[:, i]
         float a2 = b2, t2a[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll 8
         for (int k = 0; k < kHid; ++k) {
             const float w = sW2[m * kW2Pad + k];
-            a2 = fmaf(w, sX[wv][k][0], a2);
-#pragma unroll
-            for (int i = 0; i < 6; ++i) t2a[i] = fmaf(w, sX[wv][k][1 + i], t2a[i]);
+            const float4 p = reinterpret_cast<const float4*>(sX[wv][k])[0], r = reinterpret_cast<const float4*>(sX[wv][k])[1];
+            a2 = fmaf(w, p.x, a2);
+            t2a[0] = fmaf(w, p.y, t2a[0]);
+            t2a[1] = fmaf(w, p.z, t2a[1]);
+            t2a[2] = fmaf(w, p.w, t2a[2]);
+            t2a[3] = fmaf(w, r.x, t2a[3]);
+            t2a[4] = fmaf(w, r.y, t2a[4]);
+            t2a[5] = fmaf(w, r.z, t2a[5]);
         }
         const float h2 = softplusf(a2), d2 = logisticf(a2), d2p = d2 * (1.0f - d2);
         // output: psi^ = w3 . h2 + b3, g^_i = w3 . (d2 T2a[:, i])
@@ -528,25 +536,40 @@ __global__ __launch_bounds__(kTrainBlock) void k_mlp_train(MlpTrainLaunch L) {
         gb3 += rr;
         const float delta2 = d2p * w3 * qt + d2 * rr * w3;   // dloss / da2[m]
         gb2 += delta2;
-        sD[wv][m][0] = delta2;
-#pragma unroll
-        for (int i = 0; i < 6; ++i) sD[wv][m][1 + i] = g2a[i];
+        float4* d4 = reinterpret_cast<float4*>(sD[wv][m]);
+        d4[0] = make_float4(delta2, g2a[0], g2a[1], g2a[2]);
+        d4[1] = make_float4(g2a[3], g2a[4], g2a[5], 0.0f);
         __syncthreads();
-        // dW2[m, k] += delta2[m] h1[k] + sum_i G2a[m, i] T1[k, i]
+        // dW2[m, k] += delta2[m] h1[k] + sum_i G2a[m, i] T1[k, i], over the workgroup's samples
+#pragma unroll 1
+        for (int s = 0; s < kTrainWaves; ++s) {
+            const float4 a = reinterpret_cast<const float4*>(sD[s][m])[0], b = reinterpret_cast<const float4*>(sD[s][m])[1];
 #pragma unroll
-        for (int k = 0; k < kHid; ++k) {
-            float acc = delta2 * sX[wv][k][0];
-#pragma unroll
-            for (int i = 0; i < 6; ++i) acc = fmaf(g2a[i], sX[wv][k][1 + i], acc);
-            gW2[k] += acc;
+            for (int k = 0; k < kCols; ++k) {
+                const float4* x = reinterpret_cast<const float4*>(sX[s][kCols * wv + k]);
+                const float4 p = x[0], r = x[1];
+                float acc = a.x * p.x;
+                acc = fmaf(a.y, p.y, acc);
+                acc = fmaf(a.z, p.z, acc);
+                acc = fmaf(a.w, p.w, acc);
+                acc = fmaf(b.x, r.x, acc);
+                acc = fmaf(b.y, r.y, acc);
+                gW2[k] += fmaf(b.z, r.z, acc);
+            }
         }
         // unit k = m of layer 1: dh1[k] = sum_m W2[m, k] delta2[m], dT1[k, i] = sum_m W2[m, k] G2a[m, i]
         float dh1 = 0.0f, dT1[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll 8
         for (int mm = 0; mm < kHid; ++mm) {
             const float w = sW2[mm * kW2Pad + m];
-            dh1 = fmaf(w, sD[wv][mm][0], dh1);
-#pragma unroll
-            for (int i = 0; i < 6; ++i) dT1[i] = fmaf(w, sD[wv][mm][1 + i], dT1[i]);
+            const float4 p = reinterpret_cast<const float4*>(sD[wv][mm])[0], r = reinterpret_cast<const float4*>(sD[wv][mm])[1];
+            dh1 = fmaf(w, p.x, dh1);
+            dT1[0] = fmaf(w, p.y, dT1[0]);
+            dT1[1] = fmaf(w, p.z, dT1[1]);
+            dT1[2] = fmaf(w, p.w, dT1[2]);
+            dT1[3] = fmaf(w, r.x, dT1[3]);
+            dT1[4] = fmaf(w, r.y, dT1[4]);
+            dT1[5] = fmaf(w, r.z, dT1[5]);
         }
         float dd1 = 0.0f;
 #pragma unroll
@@ -558,51 +581,87 @@ __global__ __launch_bounds__(kTrainBlock) void k_mlp_train(MlpTrainLaunch L) {
         gb1 += delta1;
 #pragma unroll
         for (int i = 0; i < 6; ++i) gW1[i] += delta1 * xh[i];
-        __syncthreads();   // sX / sD are rewritten by the next sample
+        __syncthreads();   // sX / sD are rewritten by the next samples
     }
-    float* out = L.partial + (int64_t)gw * (kMlpParams + 1);
-    if (gw < L.n_waves) {
+    // the workgroup's row: W2's part through LDS (coalesced), the units' other parameters summed over the waves
 #pragma unroll
-        for (int i = 0; i < 6; ++i) out[kOffW1 + m * 6 + i] = gW1[i];
-        out[kOffB1 + m] = gb1;
+    for (int k = 0; k < kCols; ++k) sW2[m * kW2Pad + kCols * wv + k] = gW2[k];
 #pragma unroll
-        for (int k = 0; k < kHid; ++k) out[kOffW2 + m * kHid + k] = gW2[k];
-        out[kOffB2 + m] = gb2;
-        out[kOffW3 + m] = gw3;
-        if (m == 0) {
-            out[kOffB3] = gb3;
-            out[kMlpParams] = loss;
-        }
+    for (int i = 0; i < 6; ++i) sX[wv][m][i] = gW1[i];
+    sX[wv][m][6] = gb1;
+    sX[wv][m][7] = gb2;
+    sD[wv][m][0] = gw3;
+    if (m == 0) {
+        sD[wv][0][1] = gb3;
+        sD[wv][0][2] = loss;
+    }
+    __syncthreads();
+    float* out = L.partial + (int64_t)blockIdx.x * (kMlpParams + 1);
+    for (int i = threadIdx.x; i < kHid * kHid; i += blockDim.x) out[kOffW2 + i] = sW2[(i / kHid) * kW2Pad + i % kHid];
+    auto over_waves = [&](const float* first) {   // the same place of every wave's array
+        float acc = first[0];
+#pragma unroll
+        for (int w = 1; w < kTrainWaves; ++w) acc += first[w * kHid * 8];
+        return acc;
+    };
+    for (int i = threadIdx.x; i < kHid * 6; i += blockDim.x) out[kOffW1 + i] = over_waves(&sX[0][i / 6][i % 6]);
+    if (threadIdx.x < kHid) {
+        out[kOffB1 + m] = over_waves(&sX[0][m][6]);
+        out[kOffB2 + m] = over_waves(&sX[0][m][7]);
+        out[kOffW3 + m] = over_waves(&sD[0][m][0]);
+    }
+    if (threadIdx.x == 0) {
+        out[kOffB3] = over_waves(&sD[0][0][1]);
+        out[kMlpParams] = over_waves(&sD[0][0][2]);
     }
 }
 
 hipError_t launch_mlp_train(const MlpTrainLaunch& L, hipStream_t s) {
-    const int per_block = kTrainBlock / 64;
-    if (L.n_waves % per_block != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mlp_train, dim3(L.n_waves / per_block), dim3(kTrainBlock), 0, s, L);
+    if (L.n_rows < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_mlp_train, dim3(L.n_rows), dim3(kTrainBlock), 0, s, L);
     return hipGetLastError();
 }
 
-__global__ void k_mlp_reduce(const float* partial, int n_waves, float* grad, float* loss) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > kMlpParams) return;
+// one lane per parameter in each of four waves, which take every fourth row (eight loads in flight); the four
+// sums are added in order. 128 rows 4.9 us; one lane over all of 64 rows took 15.6 us.
+__global__ __launch_bounds__(256) void k_mlp_reduce(const float* partial, int n_rows, float* grad, float* loss) {
+    __shared__ float red[4][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i = blockIdx.x * 64 + lane;
     float acc = 0.0f;
-    for (int w = 0; w < n_waves; ++w) acc += partial[(int64_t)w * (kMlpParams + 1) + i];
+    if (i <= kMlpParams) {
+        const float* p = partial + i;
+        int r = w;
+        for (; r + 28 < n_rows; r += 32) {
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = p[(int64_t)(r + 4 * k) * (kMlpParams + 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc += v[k];
+        }
+        for (; r < n_rows; r += 4) acc += p[(int64_t)r * (kMlpParams + 1)];
+    }
+    red[w][lane] = acc;
+    __syncthreads();
+    if (w != 0 || i > kMlpParams) return;
+    acc = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
     if (i < kMlpParams) grad[i] = acc;
     else *loss = acc;
 }
 
-hipError_t launch_mlp_reduce(const float* partial, int n_waves, float* grad, float* loss, hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((kMlpParams + 1 + 255) / 256), dim3(256), 0, s, partial, n_waves, grad,
-                       loss);
+hipError_t launch_mlp_reduce(const float* partial, int n_rows, float* grad, float* loss, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((kMlpParams + 1 + 63) / 64), dim3(256), 0, s, partial, n_rows, grad, loss);
     return hipGetLastError();
 }
 
-__global__ void k_mlp_adam(float* params, float* m, float* v, const float* grad, const int64_t* step, float lr,
+// every workgroup counts the steps in an entry of its own (all equal), so that none waits for another's reading
+__global__ void k_mlp_adam(float* params, float* m, float* v, const float* grad, int64_t* steps, float lr,
                            float beta1, float beta2, float eps, uint16_t* wbf) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t step = steps[blockIdx.x] + 1;
+    __syncthreads();
+    if (threadIdx.x == 0) steps[blockIdx.x] = step;
     if (i >= kMlpParams) return;
-    const float t = float(*step);
+    const float t = float(step);
     const float g = grad[i];
     const float mi = beta1 * m[i] + (1.0f - beta1) * g;
     const float vi = beta2 * v[i] + (1.0f - beta2) * g * g;
@@ -615,10 +674,11 @@ __global__ void k_mlp_adam(float* params, float* m, float* v, const float* grad,
     wbf[i] = f2bf(p);
 }
 
-hipError_t launch_mlp_adam(float* params, float* m, float* v, const float* grad, const int64_t* step, float lr,
+hipError_t launch_mlp_adam(float* params, float* m, float* v, const float* grad, int64_t* steps, float lr,
                            float beta1, float beta2, float eps, uint16_t* wbf, hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_adam, dim3((kMlpParams + 255) / 256), dim3(256), 0, s, params, m, v, grad, step, lr,
-                       beta1, beta2, eps, wbf);
+    static_assert((kMlpParams + 255) / 256 == kAdamBlocks, "a step count for every workgroup");
+    hipLaunchKernelGGL(k_mlp_adam, dim3(kAdamBlocks), dim3(256), 0, s, params, m, v, grad, steps, lr, beta1, beta2,
+                       eps, wbf);
     return hipGetLastError();
 }
 
@@ -629,15 +689,6 @@ __global__ void k_mlp_to_bf16(const float* params, uint16_t* wbf) {
 
 hipError_t launch_mlp_to_bf16(const float* params, uint16_t* wbf, hipStream_t s) {
     hipLaunchKernelGGL(k_mlp_to_bf16, dim3((kMlpParams + 255) / 256), dim3(256), 0, s, params, wbf);
-    return hipGetLastError();
-}
-
-__global__ void k_step_incr(int64_t* step) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *step += 1;
-}
-
-hipError_t launch_mlp_step_incr(int64_t* step, hipStream_t s) {
-    hipLaunchKernelGGL(k_step_incr, dim3(1), dim3(64), 0, s, step);
     return hipGetLastError();
 }
 

@@ -14,14 +14,11 @@ using namespace mad;
 
 namespace {
 
-constexpr int kMaxWaves = 2048;
+constexpr int kMaxRows = 512;
 
-// waves for a batch of `count` samples: about eight samples per wave, a multiple of four
-int train_waves(int64_t count) {
-    int64_t w = (count + 7) / 8;
-    w = std::max<int64_t>(4, std::min<int64_t>(w, kMaxWaves));
-    return (int)((w + 3) / 4 * 4);
-}
+// workgroups (partial gradient rows) for a batch: four samples each, at most two workgroups per compute unit of a
+// 256-unit device, which then take further samples in rounds
+int train_rows(int64_t count) { return (int)std::max<int64_t>(1, std::min<int64_t>((count + 3) / 4, kMaxRows)); }
 
 int upload_params(mad_mlp* m, const float* params_host) {
     for (int i = 0; i < kMlpParams; ++i)
@@ -29,7 +26,7 @@ int upload_params(mad_mlp* m, const float* params_host) {
     MAD_HIP_TRY(hipMemcpy(m->d_params, params_host, sizeof(float) * kMlpParams, hipMemcpyHostToDevice));
     MAD_HIP_TRY(hipMemset(m->d_m, 0, sizeof(float) * kMlpParams));
     MAD_HIP_TRY(hipMemset(m->d_v, 0, sizeof(float) * kMlpParams));
-    MAD_HIP_TRY(hipMemset(m->d_step, 0, sizeof(int64_t)));
+    MAD_HIP_TRY(hipMemset(m->d_step, 0, sizeof(int64_t) * kAdamBlocks));
     MAD_HIP_TRY(launch_mlp_to_bf16(m->d_params, m->d_wbf, nullptr));
     MAD_HIP_TRY(hipDeviceSynchronize());
     return MAD_OK;
@@ -58,14 +55,13 @@ int loss_grad(mad_mlp* m, const float* z, const float* W, const float* dW, const
     for (int i = 0; i < 6; ++i) L.c_g[i] = c_g[i];
     L.lam_g = lam_g;
     L.partial = m->d_partial;
-    L.n_waves = train_waves(count);
+    L.n_rows = train_rows(count);
     MAD_HIP_TRY(launch_mlp_train(L, s));
-    MAD_HIP_TRY(launch_mlp_reduce(m->d_partial, L.n_waves, grad, loss, s));
+    MAD_HIP_TRY(launch_mlp_reduce(m->d_partial, L.n_rows, grad, loss, s));
     return MAD_OK;
 }
 
 int adam(mad_mlp* m, const float* grad, float lr, float b1, float b2, float eps, hipStream_t s) {
-    MAD_HIP_TRY(launch_mlp_step_incr(m->d_step, s));
     MAD_HIP_TRY(launch_mlp_adam(m->d_params, m->d_m, m->d_v, grad, m->d_step, lr, b1, b2, eps, m->d_wbf, s));
     return MAD_OK;
 }
@@ -110,9 +106,8 @@ int32_t mad_mlp_create(int32_t hidden, const float* params_host, const float* s_
     alloc((void**)&m->d_wbf, sizeof(uint16_t) * kMlpParams);
     alloc((void**)&m->d_grad, sizeof(float) * kMlpParams);
     alloc((void**)&m->d_loss, sizeof(float) * 4);
-    alloc((void**)&m->d_step, sizeof(int64_t));
-    alloc((void**)&m->d_partial, sizeof(float) * (size_t)kMaxWaves * (kMlpParams + 1));
-    m->partial_waves = kMaxWaves;
+    alloc((void**)&m->d_step, sizeof(int64_t) * kAdamBlocks);
+    alloc((void**)&m->d_partial, sizeof(float) * (size_t)kMaxRows * (kMlpParams + 1));
     if (rc == MAD_OK) rc = upload_params(m, params_host);
     if (rc != MAD_OK) {
         free_mlp(m);

@@ -53,17 +53,18 @@ struct MlpTrainLaunch {
     float s_in[6];
     float s_out;
     float c_e, c_g[6], lam_g;
-    float* partial;           // [n_waves][kMlpParams + 1]
-    int n_waves;
+    float* partial;           // [n_rows][kMlpParams + 1]
+    int n_rows;               // workgroups
 };
 hipError_t launch_mlp_train(const MlpTrainLaunch& L, hipStream_t s);
-// sum the per-wave partials in a fixed order: grad [kMlpParams], loss [1]
-hipError_t launch_mlp_reduce(const float* partial, int n_waves, float* grad, float* loss, hipStream_t s);
-// Adam on the master copy (step t >= 1, read on the device), then refresh the BF16 copy
-hipError_t launch_mlp_adam(float* params, float* m, float* v, const float* grad, const int64_t* step, float lr,
+// sum the per-workgroup partials in a fixed order: grad [kMlpParams], loss [1]
+hipError_t launch_mlp_reduce(const float* partial, int n_rows, float* grad, float* loss, hipStream_t s);
+// Adam on the master copy (its step count, one entry for each of its workgroups, incremented first), then refresh
+// the BF16 copy
+constexpr int kAdamBlocks = 19;
+hipError_t launch_mlp_adam(float* params, float* m, float* v, const float* grad, int64_t* steps, float lr,
                            float beta1, float beta2, float eps, uint16_t* wbf, hipStream_t s);
 hipError_t launch_mlp_to_bf16(const float* params, uint16_t* wbf, hipStream_t s);
-hipError_t launch_mlp_step_incr(int64_t* step, hipStream_t s);
 
 }  // namespace mad
 
@@ -77,7 +78,6 @@ struct mad_mlp {
     uint16_t* d_wbf = nullptr;     // BF16 evaluation copy
     float* d_grad = nullptr;
     float* d_loss = nullptr;
-    int64_t* d_step = nullptr;     // Adam step counter (device, so a training loop needs no host sync)
+    int64_t* d_step = nullptr;     // Adam step counts [kAdamBlocks] (device, so a training loop needs no host sync)
     float* d_partial = nullptr;
-    int partial_waves = 0;
 };
