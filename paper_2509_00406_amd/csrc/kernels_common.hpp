@@ -28,6 +28,28 @@ __device__ __forceinline__ bool finite(double v) {
     return (u & 0x7ff0000000000000ull) != 0x7ff0000000000000ull;
 }
 
+// wave-scope ordering of LDS accesses between the lanes of one wave
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// n values from LDS (16-byte aligned) to memory, a wave together, 16 bytes a lane where memory need only be
+// aligned to the value. For results that are written once, in whole lines, and not read
+// again: the stores pass by the L2, which keeps x and the element data (rows of a 1000^2 cloth: 187 -> 146 us).
+template <typename T>
+__device__ __forceinline__ void store_run(T* to, const T* from, int n, int lane) {
+    constexpr int N = 16 / sizeof(T);
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    typedef vec vec_any __attribute__((aligned(sizeof(T))));
+    const int nv = n / N;
+    for (int k = lane; k < nv; k += 64)
+        __builtin_nontemporal_store(reinterpret_cast<const vec*>(from)[k], reinterpret_cast<vec_any*>(to + k * N));
+    const int k = nv * N + lane;
+    if (k < n) __builtin_nontemporal_store(from[k], to + k);
+}
+
 // triangle quality 4 sqrt(3) A / (l0^2 + l1^2 + l2^2): 1 for equilateral, 0 for degenerate
 __device__ __forceinline__ double tri_quality3(const double* a, const double* b, const double* c) {
     const double e1[3] = {b[0] - a[0], b[1] - a[1], b[2] - a[2]};

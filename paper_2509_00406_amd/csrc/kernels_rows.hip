@@ -11,10 +11,11 @@
 // gradient in LDS, the lanes then share out the (row, component) sums over the row's lanes, and the blocks leave
 // through LDS in the order of memory (a unit's blocks are one contiguous range).
 //
-// 1000^2 cloth (2,996,001 springs, 1,000,000 vertex terms, FP32, clamped): 137 us where the patch kernel took 344
-// and its gather 26; 392 MB that it cannot do without, 2.9 TB/s. Two thirds of the cycles issue a vector
-// instruction at four waves per SIMD (113 registers); held to five waves it spills (160 us). Loading a unit's
-// columns while the unit before is worked on took 10 us off.
+// 1000^2 cloth (2,996,001 springs, 1,000,000 vertex terms, FP32, clamped): 175 us on inputs that no cache holds
+// (140 us on warm ones) where the patch kernel took 344 and its gather 26; it moves 162 MB in and 280 MB out of
+// the 392 MB that it cannot do without, 2.5 TB/s. Each unit's columns are loaded while the unit before it is worked
+// on, and the row sums keep eight LDS reads in flight (189 -> 179 us); five waves per SIMD (96 registers) against
+// four 200 -> 179 us, six spill.
 #include "kernels_common.hpp"
 
 namespace mad {
@@ -24,39 +25,19 @@ namespace {
 constexpr int kRowWaves = kBlock / 64;
 constexpr int kRowComps = 9;   // diagonal block (upper half: 6 in 3D) or product (3), then the gradient (3)
 
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// n values from LDS (16-byte aligned) to memory, a wave together, 16 bytes a lane where memory need only be
-// aligned to the value. The Hessian is written once and not read here: the stores pass by the L2, which keeps x
-// and the element data (1000^2 cloth: 187 -> 146 us).
-template <typename T>
-__device__ __forceinline__ void store_run(T* to, const T* from, int n, int lane) {
-    constexpr int N = 16 / sizeof(T);
-    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
-    typedef vec vec_any __attribute__((aligned(sizeof(T))));
-    const int nv = n / N;
-    for (int k = lane; k < nv; k += 64)
-        __builtin_nontemporal_store(reinterpret_cast<const vec*>(from)[k], reinterpret_cast<vec_any*>(to + k * N));
-    const int k = nv * N + lane;
-    if (k < n) __builtin_nontemporal_store(from[k], to + k);
-}
-
 // An edge term is a function of the edge's length l: its gradient lies along the edge's unit vector u and its
 // Hessian is along u u^T + across (I - u u^T). The derivatives are forward mode over the edge's own axes,
 // where the two coordinates across it vanish (element.hpp). Terms add up as these numbers.
+// A vertex term is a quadratic with an isotropic Hessian (along = across).
 template <typename T>
-struct EdgePart {
+struct RowPart {
     double f;
     T g[3], along, across;   // g: gradient at the column's vertex
 };
 
 template <class Term, typename T, int MODE>
-__device__ __forceinline__ void add_edge(const RowTerm& A, const double (&in)[2], const double (&r)[3], double l,
-                                         const T (&u)[3], T te, EdgePart<T>& P) {
+__device__ __forceinline__ void add_edge(const RowTerm& A, const double (&in)[4], const double (&r)[3], double l,
+                                         const T (&u)[3], T te, RowPart<T>& P) {
     static_assert(Term::NREST <= 2 && Term::NS == 2 && Term::FRAME == 3, "an edge term");
     const double rest[2] = {in[0], in[1]};
     T h0 = T(0), h1 = T(0);
@@ -111,16 +92,9 @@ __device__ __forceinline__ void add_edge(const RowTerm& A, const double (&in)[2]
     P.across += h1;
 }
 
-// A vertex term here is a quadratic with an isotropic Hessian h I.
-template <typename T>
-struct VertexPart {
-    double f;
-    T g[3], h;
-};
-
 template <class Term, typename T, int MODE>
 __device__ __forceinline__ void add_vertex(const RowTerm& A, const double (&in)[4], const double (&x)[3], T te,
-                                           VertexPart<T>& P) {
+                                           RowPart<T>& P) {
     static_assert(Term::NVD == 4 && Term::NS == 1 && Term::NREST == 0, "a vertex term");
     if constexpr (MODE == 0) {
         P.f += Term::template energy<double>(x, in, A.prm);
@@ -138,7 +112,9 @@ __device__ __forceinline__ void add_vertex(const RowTerm& A, const double (&in)[
             for (int c = 0; c < 3; ++c) P.g[c] += T(res[m].v) * res[m].g[c];
             h += res[m].g[0] * res[m].g[0];
         }
-        P.h += MODE == 3 ? fmax(h, te) : h;
+        h = MODE == 3 ? fmax(h, te) : h;
+        P.along += h;
+        P.across += h;
     } else {
         using S = typename std::conditional<MODE == 1, D1<3, T>, HD<3, T>>::type;
         const S q[3] = {var<S>(0, x[0]), var<S>(1, x[1]), var<S>(2, x[2])};
@@ -146,12 +122,16 @@ __device__ __forceinline__ void add_vertex(const RowTerm& A, const double (&in)[
         P.f += f.v;
 #pragma unroll
         for (int c = 0; c < 3; ++c) P.g[c] += f.g[c];
-        if constexpr (MODE >= 2) P.h += MODE == 3 ? fmax(f.h[0], te) : f.h[0];
+        if constexpr (MODE >= 2) {
+            const T h = MODE == 3 ? fmax(f.h[0], te) : f.h[0];
+            P.along += h;
+            P.across += h;
+        }
     }
 }
 
 // what an edge or vertex term reads per element: its rest data (edge), its vertex data (vertex)
-__device__ __forceinline__ void edge_inputs(const RowTerm& A, int edge, double (&in)[2]) {
+__device__ __forceinline__ void edge_inputs(const RowTerm& A, int edge, double (&in)[4]) {
     in[0] = A.nrest > 0 ? A.rest[edge] : 0.0;
     in[1] = A.nrest > 1 ? A.rest[A.n + edge] : 0.0;
 }
@@ -161,7 +141,7 @@ __device__ __forceinline__ void vertex_inputs(const RowTerm& A, int row, double 
 }
 
 template <typename T, int MODE>
-__global__ __launch_bounds__(kBlock) void k_eval_rows(RowLaunch L) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 3))) void k_eval_rows(RowLaunch L) {
     __shared__ __align__(16) T s_part[kRowWaves][64 * kRowComps];   // the lanes' contributions, then the unit's blocks
     __shared__ T s_sum[kRowWaves][64 * kRowComps];    // the rows' sums
     __shared__ int s_off[kRowWaves][65];              // first block of each row, from the unit's first
@@ -219,13 +199,13 @@ __global__ __launch_bounds__(kBlock) void k_eval_rows(RowLaunch L) {
                 edge = have ? L.edge[k0 + p0 + lane] : -1;
             }
             const bool is_edge = have && edge >= 0;
-            double xc[3] = {0.0, 0.0, 0.0}, xr[3] = {0.0, 0.0, 0.0}, ein[2] = {0.0, 0.0};
-            double vin[4] = {0.0, 0.0, 0.0, 0.0};
+            double xc[3] = {0.0, 0.0, 0.0}, xr[3] = {0.0, 0.0, 0.0};
+            double in[4] = {0.0, 0.0, 0.0, 0.0};   // the element data of the lane's first term
             if (have) {
 #pragma unroll
                 for (int c = 0; c < 3; ++c) xc[c] = L.x[(int64_t)col * 3 + c];
             }
-            if (is_edge && L.n_edge > 0) edge_inputs(L.edges[0], edge, ein);
+            if (is_edge && L.n_edge > 0) edge_inputs(L.edges[0], edge, in);
             // the row of every lane: row starts as bits of a mask
             s_start[w][lane] = 0;
             wave_sync();
@@ -241,10 +221,9 @@ __global__ __launch_bounds__(kBlock) void k_eval_rows(RowLaunch L) {
 #pragma unroll
                 for (int c = 0; c < 3; ++c) xr[c] = L.x[(int64_t)row * 3 + c];
             }
-            if (dia && L.n_vert > 0) vertex_inputs(L.verts[0], row, vin);
+            if (dia && L.n_vert > 0) vertex_inputs(L.verts[0], row, in);
             if (p0 == 0 && more) fetch_lanes(next_at, next_to, next_col, next_edge, next_start);
-            EdgePart<T> E{};
-            VertexPart<T> V{};
+            RowPart<T> P{};
             T d[3] = {T(0), T(0), T(0)}, fl = T(0);   // u; floor of the translations, summed over the edge terms
             if (is_edge) {
                 double r[3];   // from the row's vertex to the column's
@@ -253,35 +232,31 @@ __global__ __launch_bounds__(kBlock) void k_eval_rows(RowLaunch L) {
                 const double rr = dot3(r, r), il = rr > 0.0 ? frsq(rr) : 0.0, l = length_of(rr, il);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) d[c] = rr > 0.0 ? T(r[c] * il) : T(c == 0 ? 1 : 0);
-                for (int t = 0; t < L.n_edge; ++t) {
+                for (int t = 0; t < L.n_edge;) {
                     const RowTerm& A = L.edges[t];
-                    if (t > 0) edge_inputs(A, edge, ein);
-                    if (A.kind == K_SPRING) add_edge<TermSpring, T, MODE>(A, ein, r, l, d, te, E);
-                    else if (A.kind == K_RES_EDGE) add_edge<TermResEdge, T, MODE>(A, ein, r, l, d, te, E);
-                    else add_edge<TermEdgeSqlen, T, MODE>(A, ein, r, l, d, te, E);
+                    if (A.kind == K_SPRING) add_edge<TermSpring, T, MODE>(A, in, r, l, d, te, P);
+                    else if (A.kind == K_RES_EDGE) add_edge<TermResEdge, T, MODE>(A, in, r, l, d, te, P);
+                    else add_edge<TermEdgeSqlen, T, MODE>(A, in, r, l, d, te, P);
                     if (MODE == 3) fl += T(0.5) * te;
+                    if (++t < L.n_edge) edge_inputs(L.edges[t], edge, in);
                 }
-                esum += row < col ? E.f : 0.0;
-                bad = bad || !finite(E.f) || !finite(fabs(E.g[0]) + fabs(E.g[1]) + fabs(E.g[2]) + fabs(E.along) + fabs(E.across));
-            }
-            if (dia) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) bad = bad || !finite(xr[c]);
-                for (int t = 0; t < L.n_vert; ++t) {
+            } else if (dia) {
+                for (int t = 0; t < L.n_vert;) {
                     const RowTerm& A = L.verts[t];
-                    if (t > 0) vertex_inputs(A, row, vin);
-                    if (A.kind == K_INERTIA) add_vertex<TermInertia, T, MODE>(A, vin, xr, te, V);
-                    else add_vertex<TermResPosition, T, MODE>(A, vin, xr, te, V);
+                    if (A.kind == K_INERTIA) add_vertex<TermInertia, T, MODE>(A, in, xr, te, P);
+                    else add_vertex<TermResPosition, T, MODE>(A, in, xr, te, P);
+                    if (++t < L.n_vert) vertex_inputs(L.verts[t], row, in);
                 }
-                esum += V.f;
-                bad = bad || !finite(V.f) || !finite(fabs(V.g[0]) + fabs(V.g[1]) + fabs(V.g[2]) + fabs(V.h));
             }
+            esum += row <= col ? P.f : 0.0;
+            bad = bad || !finite(P.f) || !finite(fabs(P.g[0]) + fabs(P.g[1]) + fabs(P.g[2]) + fabs(P.along) + fabs(P.across)) ||
+                  !finite(xr[0]) || !finite(xr[1]) || !finite(xr[2]);
             // the row's own part of the element: gradient, and diagonal block or product
             T* to = part + lane * kRowComps;
             if constexpr (MODE >= 1) {
                 if (have && L.want_grad)
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) to[6 + c] = V.g[c] - E.g[c];
+                    for (int c = 0; c < 3; ++c) to[6 + c] = dia ? P.g[c] : -P.g[c];
             }
             if constexpr (MODE >= 2) {
                 if (have && L.hvp) {
@@ -289,20 +264,20 @@ __global__ __launch_bounds__(kBlock) void k_eval_rows(RowLaunch L) {
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
                         vr[c] = T(L.v[(int64_t)row * 3 + c]);
-                        vc[c] = T(L.v[(int64_t)col * 3 + c]);
+                        vc[c] = dia ? T(0) : T(L.v[(int64_t)col * 3 + c]);
                         along += d[c] * (vr[c] - vc[c]);
                     }
-                    along *= E.along - E.across;
+                    along *= P.along - P.across;
 #pragma unroll
                     for (int c = 0; c < 3; ++c)
-                        to[c] = V.h * vr[c] + E.across * (vr[c] - vc[c]) + along * d[c] + fl * (vr[c] + vc[c]);
+                        to[c] = P.across * (vr[c] - vc[c]) + along * d[c] + fl * (vr[c] + vc[c]);
                 } else if (have) {
 #pragma unroll
                     for (int a = 0; a < 3; ++a)
 #pragma unroll
                         for (int b = a; b < 3; ++b)
                             to[Packed<3>::at(a, b)] =
-                                (E.along - E.across) * d[a] * d[b] + (a == b ? V.h + E.across + fl : T(0));
+                                (P.along - P.across) * d[a] * d[b] + (a == b ? P.across + fl : T(0));
                 }
             }
             if constexpr (MODE >= 1) {
@@ -313,7 +288,13 @@ __global__ __launch_bounds__(kBlock) void k_eval_rows(RowLaunch L) {
                         const int j = k / NC, c = c0 + k - j * NC;
                         const int b = max(off[j] - p0, 0), e = min(off[j + 1] - p0, 64);
                         T acc = single ? T(0) : sum[j * kRowComps + c];
-                        for (int l = b; l < e; ++l) acc += part[l * kRowComps + c];
+                        for (int l = b; l < e; l += 8) {   // eight reads in flight, added in order
+                            T q[8];
+#pragma unroll
+                            for (int m = 0; m < 8; ++m) q[m] = part[min(l + m, e - 1) * kRowComps + c];
+#pragma unroll
+                            for (int m = 0; m < 8; ++m) acc += l + m < e ? q[m] : T(0);
+                        }
                         sum[j * kRowComps + c] = acc;
                     }
                 };
@@ -334,7 +315,7 @@ __global__ __launch_bounds__(kBlock) void k_eval_rows(RowLaunch L) {
                         for (int a = 0; a < 3; ++a)
 #pragma unroll
                             for (int b = 0; b < 3; ++b) {
-                                const T o = (E.across - E.along) * d[a] * d[b] + (a == b ? fl - E.across : T(0));
+                                const T o = (P.across - P.along) * d[a] * d[b] + (a == b ? fl - P.across : T(0));
                                 blk[3 * a + b] = dia ? q[Packed<3>::at(a, b)] : o;
                             }
                         if (single) {
