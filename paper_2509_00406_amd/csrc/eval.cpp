@@ -91,7 +91,7 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
     if (rows) {
         // Edge and vertex terms only: the row-owned kernel, which evaluates an edge from both of its rows and
         // needs no accumulation between workgroups. FP32, clamped, against the patch kernel and its gather:
-        // 1000^2 cloth 322 -> 143 us, 250^2 41 -> 18 us, 50^2 23 -> 12 us; 1000^2 FP64 485 -> 240 us.
+        // 1000^2 cloth 322 -> 150 us, 250^2 41 -> 17 us, 50^2 23 -> 12 us; 1000^2 FP64 485 -> 231 us (one state repeated).
         RowLaunch L{};
         L.prec = p->prec;
         L.mode = kmode;
