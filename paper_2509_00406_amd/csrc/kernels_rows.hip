@@ -37,7 +37,7 @@ struct RowPart {
 
 template <class Term, typename T, int MODE>
 __device__ __forceinline__ void add_edge(const RowTerm& A, const double (&in)[4], const double (&r)[3], double l,
-                                         const T (&u)[3], T te, RowPart<T>& P) {
+                                         const T (&u)[3], double il, T te, RowPart<T>& P) {
     static_assert(Term::NREST <= 2 && Term::NS == 2 && Term::FRAME == 3, "an edge term");
     const double rest[2] = {in[0], in[1]};
     T h0 = T(0), h1 = T(0);
@@ -80,7 +80,7 @@ __device__ __forceinline__ void add_edge(const RowTerm& A, const double (&in)[4]
     if constexpr (sizeof(T) == 4) {
         P.f += fl;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) P.g[c] += gu * u[c];
+        for (int c = 0; c < 3; ++c) P.g[c] += T((double)gu * (r[c] * il));
     }
     if constexpr (MODE == 3) {
         // clamped in the orthonormal coordinate (x_1 - x_0) / sqrt(2), whose Hessian is twice this one; the
@@ -234,9 +234,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                 for (int c = 0; c < 3; ++c) d[c] = rr > 0.0 ? T(r[c] * il) : T(c == 0 ? 1 : 0);
                 for (int t = 0; t < L.n_edge;) {
                     const RowTerm& A = L.edges[t];
-                    if (A.kind == K_SPRING) add_edge<TermSpring, T, MODE>(A, in, r, l, d, te, P);
-                    else if (A.kind == K_RES_EDGE) add_edge<TermResEdge, T, MODE>(A, in, r, l, d, te, P);
-                    else add_edge<TermEdgeSqlen, T, MODE>(A, in, r, l, d, te, P);
+                    if (A.kind == K_SPRING) add_edge<TermSpring, T, MODE>(A, in, r, l, d, il, te, P);
+                    else if (A.kind == K_RES_EDGE) add_edge<TermResEdge, T, MODE>(A, in, r, l, d, il, te, P);
+                    else add_edge<TermEdgeSqlen, T, MODE>(A, in, r, l, d, il, te, P);
                     if (MODE == 3) fl += T(0.5) * te;
                     if (++t < L.n_edge) edge_inputs(L.edges[t], edge, in);
                 }
@@ -282,27 +282,28 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
             }
             if constexpr (MODE >= 1) {
                 wave_sync();
-                auto row_sums = [&](auto count, int c0) {
+                auto row_sums = [&](auto count, auto zero, int c0) {
+                    using A = decltype(zero);
                     constexpr int NC = decltype(count)::value;
                     for (int k = lane; k < nrows * NC; k += 64) {
                         const int j = k / NC, c = c0 + k - j * NC;
                         const int b = max(off[j] - p0, 0), e = min(off[j + 1] - p0, 64);
-                        T acc = single ? T(0) : sum[j * kRowComps + c];
+                        A acc = single ? A(0) : A(sum[j * kRowComps + c]);
                         for (int l = b; l < e; l += 8) {   // eight reads in flight, added in order
                             T q[8];
 #pragma unroll
                             for (int m = 0; m < 8; ++m) q[m] = part[min(l + m, e - 1) * kRowComps + c];
 #pragma unroll
-                            for (int m = 0; m < 8; ++m) acc += l + m < e ? q[m] : T(0);
+                            for (int m = 0; m < 8; ++m) acc += l + m < e ? A(q[m]) : A(0);
                         }
-                        sum[j * kRowComps + c] = acc;
+                        sum[j * kRowComps + c] = T(acc);
                     }
                 };
                 if constexpr (MODE >= 2) {
-                    if (L.hvp) row_sums(std::integral_constant<int, 3>{}, 0);
-                    else row_sums(std::integral_constant<int, 6>{}, 0);
+                    if (L.hvp) row_sums(std::integral_constant<int, 3>{}, T(0), 0);
+                    else row_sums(std::integral_constant<int, 6>{}, T(0), 0);
                 }
-                if (L.want_grad) row_sums(std::integral_constant<int, 3>{}, 6);
+                if (L.want_grad) row_sums(std::integral_constant<int, 3>{}, 0.0, 6);
                 wave_sync();
             }
             if constexpr (MODE >= 2) {
