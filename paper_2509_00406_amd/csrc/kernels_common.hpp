@@ -156,15 +156,16 @@ __device__ __forceinline__ void block_reduce_store(double v, double* red, double
     if (threadIdx.x == 0) *out = red[0];
 }
 
-// sum of red[0, kBlock) in a fixed tree order, whatever the workgroup size (at least kBlock threads, all of
-// them calling); red is already filled and visible to every lane
-__device__ __forceinline__ void block_sum_store(double* red, double* out) {
+// sum of red[0, kBlock) in a fixed tree order, by the workgroup's first wave (no barrier: the tree's upper two
+// levels are each lane's own four values, the others shuffles); red is already filled and visible
+__device__ __forceinline__ void block_sum_store(const double* red, double* out) {
+    static_assert(kBlock == 256, "four values per lane");
+    if (threadIdx.x >= 64) return;
+    const int l = threadIdx.x;
+    double v = (red[l] + red[l + 128]) + (red[l + 64] + red[l + 192]);
 #pragma unroll
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = red[0];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
+    if (l == 0) *out = v;
 }
 
 }  // namespace mad

@@ -63,6 +63,24 @@ __device__ __forceinline__ int wave_max(int v) {
     return v;
 }
 
+// where an element's blocks are in the patch, and its segment
+template <class Term>
+struct BlockSlots {
+    static constexpr int NP = Term::NS * (Term::NS + 1) / 2;
+    uint32_t w[NP];
+    int seg;
+    __device__ __forceinline__ void load(const PatchTermArgs& A, int e) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) w[k] = A.lslot[(int64_t)k * A.n + e];
+        seg = A.lseg[e];
+    }
+};
+
+// They are asked for before the element is computed where the registers are there to hold them: elements of a
+// plane or a line. A shell's kernel has none to spare.
+template <class Term>
+constexpr bool kEarlySlots = Term::D <= 2;
+
 // Add the Hessian blocks of the wave's elements (one per lane, `have` lanes only) into the patch's
 // blocks in LDS with plain read-add-writes: the lanes of one segment touch disjoint blocks, the
 // segments go one after another, and the lock keeps the other waves of the workgroup out. The block
@@ -71,23 +89,21 @@ __device__ __forceinline__ int wave_max(int v) {
 // vertex twice (two pairs landing in one block) makes the wave add pair by pair instead.
 // Called by all 64 lanes of the wave together.
 template <class Term, typename T, int MODE>
-__device__ __forceinline__ void add_blocks(const PatchLaunch& L, const PatchTermArgs& A, int e, bool have,
-                                           const ElemOut<Term, T>& o, T te, T* sh, int* lock) {
+__device__ __forceinline__ void add_blocks(const PatchLaunch& L, const PatchTermArgs& A, int e, BlockSlots<Term> in,
+                                           bool have, const ElemOut<Term, T>& o, T te, T* sh, int* lock) {
     constexpr int NS = Term::NS, D = Term::D, DD = D * D, NP = NS * (NS + 1) / 2;
-    uint32_t wv[NP];
-    int seg = -1;
     bool degen = false;
     if (have) {
+        if constexpr (!kEarlySlots<Term>) in.load(A, e);
 #pragma unroll
-        for (int k = 0; k < NP; ++k) {
-            wv[k] = A.lslot[(int64_t)k * A.n + e];
-            degen = degen || (wv[k] >> 14) == 2u;
-        }
-        seg = A.lseg[e];
+        for (int k = 0; k < NP; ++k) degen = degen || (in.w[k] >> 14) == 2u;
     } else {
 #pragma unroll
-        for (int k = 0; k < NP; ++k) wv[k] = 0u;
+        for (int k = 0; k < NP; ++k) in.w[k] = 0u;
+        in.seg = -1;
     }
+    const uint32_t (&wv)[NP] = in.w;
+    const int seg = in.seg;
     const int nseg = wave_max(seg) + 1;
     if (nseg == 0) return;
     // entry (k, c, c2) of pair k: the diagonal pairs keep their upper half (c2 >= c)
@@ -191,7 +207,11 @@ __device__ __forceinline__ void patch_term(const PatchLaunch& L, const PatchTerm
     const T te = T(L.eps > 0.0 ? L.eps : 0.0);
     ElemOut<Term, T> o{};
     bool blocks = false;   // this lane adds a Hessian into the patch's blocks
+    BlockSlots<Term> slots;
     if (e < e_end) {
+        if constexpr (MODE >= 2 && kEarlySlots<Term>) {
+            if (!L.hvp) slots.load(A, e);
+        }
         int lv[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) lv[s] = A.lvert[(int64_t)s * A.n + e];
@@ -289,7 +309,9 @@ __device__ __forceinline__ void patch_term(const PatchLaunch& L, const PatchTerm
         }
     }
     if constexpr (MODE >= 2) {
-        if (!L.hvp) add_blocks<Term, T, MODE>(L, A, e, blocks, o, te, sh, lock);
+        if (!L.hvp) {
+            add_blocks<Term, T, MODE>(L, A, e, slots, blocks, o, te, sh, lock);
+        }
     }
 }
 
@@ -306,7 +328,7 @@ __device__ __forceinline__ void eval_patch_one(const PatchLaunch& L, int p, unsi
     // matrix-free mode: the block area holds the patch's v, then its product y
     T* sy = (MODE >= 2 && L.hvp) ? sh + align16((size_t)nlv * D * sizeof(T)) / sizeof(T) : nullptr;
     if (threadIdx.x == 0) {
-        *s_next = 0;
+        *s_next = BLK / 64;   // each wave begins with the unit of its own number
         *lock = 0;
     }
     // the patch's element range of each term, in unit order (read by every unit below)
@@ -356,11 +378,8 @@ __device__ __forceinline__ void eval_patch_one(const PatchLaunch& L, int p, unsi
     // into a slot of its own, and the slots are summed in a fixed order at the end.
     static_assert(kMaxPatchUnits <= BLK, "one energy slot per unit");
     const int lane = threadIdx.x & 63;
-    for (;;) {
-        int u = 0;
-        if (lane == 0) u = atomicAdd(s_next, 1);
-        u = __builtin_amdgcn_readfirstlane(__shfl(u, 0));
-        const int unit = u;
+    for (int unit = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);;) {
+        int u = unit;
         double esum = 0.0;
         int t = -1, first = 0, last = 0;
         for (int k = 0; k < L.n_terms; ++k) {
@@ -424,66 +443,113 @@ __device__ __forceinline__ void eval_patch_one(const PatchLaunch& L, int p, unsi
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) esum += __shfl_down(esum, o);
         if (lane == 0 && unit < kMaxPatchUnits) red[unit] = esum;
+        if (lane == 0) u = atomicAdd(s_next, 1);
+        unit = __builtin_amdgcn_readfirstlane(u);
     }
     if (bad) atomicOr(L.flags, 1);
-    __syncthreads();
 
     // flush: entries only this patch touches go straight to the output; shared entries go to their
     // halo slot and are summed by the gather kernel
-    // one vertex's D gradient entries, or one row of a D x D block, per thread: the patch's index lists
-    // are read once per vertex / block row, and each thread writes D consecutive values
+    // One vertex's D gradient entries, and one block (in 3D one row of a block), per thread: the patch's index
+    // lists are read once, each thread writes consecutive values. The indices of several steps are loaded
+    // together, and those of the first ones before the wave waits for the others to finish. With a trip to memory
+    // in each step a patch of 1001^2 symmetric Dirichlet, of 43 us, spent half of them waiting: 207 -> 188 us; 1024^2
+    // shell 1295 -> 1222, 700 spheres 2537 -> 2395, 708^2 shell FP64 1920 -> 1815 us.
+    constexpr int RU = MODE >= 1 ? 2 : 1, BU = MODE >= 2 ? 4 : 1, ROWS = D == 3 ? 3 : 1;
+    int vh[RU], vg[RU], bh[BU], bg[BU], bt[BU];
+    const bool verts = MODE >= 1 && (L.want_grad || L.hvp), blocks = MODE >= 2 && !L.hvp;
+    auto vert_lists = [&](int i0) {
+#pragma unroll
+        for (int k = 0; k < RU; ++k) {
+            const int i = i0 + k * BLK;
+            if (i < nlv) {
+                vh[k] = L.lv_halo[lv0 + i];
+                vg[k] = L.lv_global[lv0 + i];
+            }
+        }
+    };
+    auto block_lists = [&](int i0) {
+#pragma unroll
+        for (int k = 0; k < BU; ++k) {
+            const int i = i0 + k * BLK;
+            if (i < nlb * ROWS) {
+                const int bl = lb0 + i / ROWS;
+                bh[k] = L.lb_halo[bl];
+                bg[k] = L.lb_gidx[bl];
+                bt[k] = L.lb_gidxT[bl];
+            }
+        }
+    };
     if constexpr (MODE >= 1) {
-        if (L.want_grad) {
+        if (verts) vert_lists(threadIdx.x);
+    }
+    if constexpr (MODE >= 2) {
+        if (blocks) block_lists(threadIdx.x);
+    }
+    __syncthreads();
+    block_sum_store(red, L.partial + p);
+    if constexpr (MODE >= 1) {
+        if (verts) {
             T* G = static_cast<T*>(L.grad);
             T* HG = static_cast<T*>(L.halo_g);
-            for (int i = threadIdx.x; i < nlv; i += BLK) {
-                const int32_t h = L.lv_halo[lv0 + i];
-                T* dst = h < 0 ? G + (int64_t)L.lv_global[lv0 + i] * D : HG + (int64_t)h * D;
-#pragma unroll
-                for (int c = 0; c < D; ++c) dst[c] = sg[i * D + c];
-            }
-        }
-    }
-    if constexpr (MODE >= 2) {
-        if (L.hvp) {
             T* Y = static_cast<T*>(L.y);
             T* HY = static_cast<T*>(L.halo_y);
-            for (int i = threadIdx.x; i < nlv * D; i += BLK) {
-                const int k = lv0 + i / D, c = i % D;
-                const int32_t h = L.lv_halo[k];
-                if (h < 0) Y[(int64_t)L.lv_global[k] * D + c] = sy[i];
-                else HY[(int64_t)h * D + c] = sy[i];
+            for (int i0 = threadIdx.x; i0 < nlv; i0 += RU * BLK) {
+                if (i0 >= RU * BLK) vert_lists(i0);
+#pragma unroll
+                for (int k = 0; k < RU; ++k) {
+                    const int i = i0 + k * BLK;
+                    if (i >= nlv) break;
+                    const int64_t to = (int64_t)(vh[k] < 0 ? vg[k] : vh[k]) * D;
+                    if (L.want_grad) {
+                        T* dst = (vh[k] < 0 ? G : HG) + to;
+#pragma unroll
+                        for (int c = 0; c < D; ++c) dst[c] = sg[i * D + c];
+                    }
+                    if constexpr (MODE >= 2) {
+                        if (L.hvp) {
+                            T* dst = (vh[k] < 0 ? Y : HY) + to;
+#pragma unroll
+                            for (int c = 0; c < D; ++c) dst[c] = sy[i * D + c];
+                        }
+                    }
+                }
             }
         }
     }
     if constexpr (MODE >= 2) {
-        if (L.hvp) {
-            block_sum_store(red, L.partial + p);
-            return;
-        }
+        if (!blocks) return;
         T* H = static_cast<T*>(L.hess);
         T* HH = static_cast<T*>(L.halo_h);
-        for (int i = threadIdx.x; i < nlb * D; i += BLK) {
-            const int bl = i / D, r = i % D;
-            const int32_t h = L.lb_halo[lb0 + bl];
-            const int32_t g = L.lb_gidx[lb0 + bl], gt = L.lb_gidxT[lb0 + bl];
-            const T* blk = sh + bl * DD;
-            // row r of the block; a diagonal block keeps only its upper half in LDS
-            T row[D];
+        for (int i0 = threadIdx.x; i0 < nlb * ROWS; i0 += BU * BLK) {
+            if (i0 >= BU * BLK) block_lists(i0);
 #pragma unroll
-            for (int c = 0; c < D; ++c) row[c] = (g == gt && c < r) ? blk[c * D + r] : blk[r * D + c];
-            T* dst = h >= 0 ? HH + (int64_t)h * DD + r * D : H + (int64_t)g * DD + r * D;
+            for (int k = 0; k < BU; ++k) {
+                const int i = i0 + k * BLK;
+                if (i >= nlb * ROWS) break;
+                const int bl = i / ROWS, r0 = i % ROWS;
+                const T* blk = sh + bl * DD;
+                T* dst = (bh[k] >= 0 ? HH + (int64_t)bh[k] * DD : H + (int64_t)bg[k] * DD) + r0 * D;
+                T* dt = H + (int64_t)bt[k] * DD + r0 * D;
+                // rows of the block (a diagonal block keeps only its upper half in LDS) and of its transpose
+                T row[DD / ROWS], tr[DD / ROWS];
 #pragma unroll
-            for (int c = 0; c < D; ++c) dst[c] = row[c];
-            if (h < 0 && gt != g) {
-                // row r of the transposed block (c, r) is column r of this one
-                T* dt = H + (int64_t)gt * DD + r * D;
+                for (int q = 0; q < D / ROWS; ++q)
 #pragma unroll
-                for (int c = 0; c < D; ++c) dt[c] = blk[c * D + r];
+                    for (int c = 0; c < D; ++c) {
+                        const int r = r0 + q;
+                        tr[q * D + c] = blk[c * D + r];
+                        row[q * D + c] = (bg[k] == bt[k] && c < r) ? tr[q * D + c] : blk[r * D + c];
+                    }
+#pragma unroll
+                for (int c = 0; c < DD / ROWS; ++c) dst[c] = row[c];
+                if (bh[k] < 0 && bt[k] != bg[k]) {
+#pragma unroll
+                    for (int c = 0; c < DD / ROWS; ++c) dt[c] = tr[c];
+                }
             }
         }
     }
-    block_sum_store(red, L.partial + p);
 }
 
 // One patch per workgroup, or (persistent) a grid sized to the device whose workgroups take their first
@@ -496,7 +562,10 @@ __device__ __forceinline__ void eval_patch_body(const PatchLaunch& L) {
     __shared__ int next, unit_next, block_lock;
     __shared__ int term_range[2 * sizeof(PatchLaunch::term_order) / sizeof(int)];   // (first, count) per term
     if (!L.persistent) {
-        eval_patch_one<T, MODE, D, FAM, BLK>(L, blockIdx.x, smem, red, &unit_next, &block_lock, term_range);
+        // neighbouring patches on one XCD, whose L2 then holds what they share (workgroups go to the XCDs in turn)
+        const int per = (int)(gridDim.x >> 3), rest8 = (int)(gridDim.x & 7), xcd = (int)(blockIdx.x & 7);
+        eval_patch_one<T, MODE, D, FAM, BLK>(L, xcd * per + min(xcd, rest8) + (int)(blockIdx.x >> 3), smem, red,
+                                             &unit_next, &block_lock, term_range);
         return;
     }
     int k = blockIdx.x;
@@ -519,8 +588,16 @@ __device__ __forceinline__ void eval_patch_body(const PatchLaunch& L) {
 // of the long dependent rotation chains).
 // BLK: threads per workgroup (the tile): 256 (four waves; two workgroups share a CU) or, for FP32, 512
 // (eight waves; one workgroup holds the CU's LDS for larger patches).
+// Waves per SIMD that an FP32 kernel is held to. Clamped and raw Hessians of a shell's elements: two (256
+// registers). Gradients in 3D: four (128 registers instead of 129), so that the four patches that a compute unit gets
+// of a mid-sized mesh run together (500^2 area gradient 52 -> 42 us with its other launches). 2D kernels take 95, five
+// waves; held to six they gain nothing.
+constexpr int patch_waves(int mode, int d, int fam) {
+    return d == 3 && fam == 0 && mode == 1 ? 4 : 2;
+}
 template <int MODE, int D, int FAM, int BLK>
-__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2))) void k_eval_patch_f32(PatchLaunch L) {
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(patch_waves(MODE, D, FAM)))) void
+k_eval_patch_f32(PatchLaunch L) {
     eval_patch_body<float, MODE, D, FAM, BLK>(L);
 }
 template <int MODE, int D, int FAM>
