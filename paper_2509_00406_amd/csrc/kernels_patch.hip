@@ -340,24 +340,27 @@ __device__ __forceinline__ void eval_patch_one(const PatchLaunch& L, int p, unsi
     }
     if (threadIdx.x < kMaxPatchUnits) red[threadIdx.x] = 0.0;   // per-unit energies
     bool bad_x = false;
-    // one vertex per thread: its index read once, its D coordinates loaded together
-    for (int i = threadIdx.x; i < nlv; i += BLK) {
-        const int64_t v = L.lv_global[lv0 + i];
+    // one vertex per thread and step: its index read once, its D coordinates loaded together, the indices of two
+    // steps in flight, and the blocks cleared while the first coordinates arrive
+    int vi[2];
+    double xv[2][D], vv[2][D];
+    auto vert_ids = [&](int i0) {
 #pragma unroll
-        for (int c = 0; c < D; ++c) {
-            const double xv = L.x[v * D + c];
-            sx[i * D + c] = xv;
-            bad_x = bad_x || !finite(xv);
-            if constexpr (MODE >= 1) sg[i * D + c] = T(0);
-            if constexpr (MODE >= 2) {
-                if (L.hvp) {
-                    sh[i * D + c] = T(L.v[v * D + c]);
-                    sy[i * D + c] = T(0);
+        for (int k = 0; k < 2; ++k) vi[k] = i0 + k * BLK < nlv ? L.lv_global[lv0 + i0 + k * BLK] : -1;
+    };
+    auto vert_loads = [&]() {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (vi[k] >= 0) {
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    xv[k][c] = L.x[(int64_t)vi[k] * D + c];
+                    if constexpr (MODE >= 2) vv[k][c] = L.hvp ? L.v[(int64_t)vi[k] * D + c] : 0.0;
                 }
             }
-        }
-    }
-    if (bad_x) atomicOr(L.flags, 1);
+    };
+    vert_ids(threadIdx.x);
+    vert_loads();
     if constexpr (MODE >= 2) {
         if (!L.hvp) {
             // 16-byte LDS writes (the block area starts 16-byte aligned), then the tail
@@ -368,6 +371,30 @@ __device__ __forceinline__ void eval_patch_one(const PatchLaunch& L, int p, unsi
             for (int i = n4 * (16 / (int)sizeof(T)) + threadIdx.x; i < nw; i += BLK) sh[i] = T(0);
         }
     }
+    for (int i0 = threadIdx.x; i0 < nlv; i0 += 2 * BLK) {
+        if (i0 >= 2 * BLK) {
+            vert_ids(i0);
+            vert_loads();
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int i = i0 + k * BLK;
+            if (i >= nlv) break;
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                sx[i * D + c] = xv[k][c];
+                bad_x = bad_x || !finite(xv[k][c]);
+                if constexpr (MODE >= 1) sg[i * D + c] = T(0);
+                if constexpr (MODE >= 2) {
+                    if (L.hvp) {
+                        sh[i * D + c] = T(vv[k][c]);
+                        sy[i * D + c] = T(0);
+                    }
+                }
+            }
+        }
+    }
+    if (bad_x) atomicOr(L.flags, 1);
     __syncthreads();
 
     bool bad = false;
