@@ -63,8 +63,12 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
     // 2.76 -> 2.57, 1001^2 symmetric Dirichlet 225 -> 216 us, 200^2 Dirichlet FP64 26 -> 21 us).
     const bool queue = p->scatter == MAD_SCATTER_PATCH && !rows &&
                        (p->persistent == 2 || (p->persistent == 1 && p->prec == MAD_F64 && d == 3 && kmode >= 2));
-    // the FP64 redo queue's count and the patch queue's head, cleared by one small kernel
-    MAD_HIP_TRY(launch_zero_counters(fallback_pass ? sc.fb_count : nullptr, queue ? sc.work_counter : nullptr, s));
+    // The patch queue's head and, in the shared static scratch, the FP64 redo queue's words are cleared by a small
+    // kernel. A problem's own redo queue is empty between evaluations: the redo pass clears what it used
+    // (a launch fewer, 4 us), unless an evaluation ended in an error before it.
+    const bool clear_fb = fallback_pass && (scp != nullptr || p->fb_unclean);
+    MAD_HIP_TRY(launch_zero_counters(clear_fb ? sc.fb_count : nullptr, queue ? sc.work_counter : nullptr, s));
+    if (fallback_pass && scp == nullptr) p->fb_unclean = true;
     if (ev) MAD_HIP_TRY(hipEventRecord((*ev)[1], s));
     // learned and analytic shell densities: vertex normals of x, then the network pass per MLP term
     if (p->shell) MAD_HIP_TRY(launch_vertex_normals(x, m.nv, p->d_vf_ptr, p->d_vf, p->d_tris, sc.normals, s));
@@ -87,7 +91,15 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
     }
     if (ev) MAD_HIP_TRY(hipEventRecord((*ev)[2], s));
     const int np = p->patches.n;
-    int n_partial_terms = (int)p->terms.size();
+    EnergyArgs E{};   // reduced beside the gather, or by its own launch
+    E.partial = sc.partial;
+    E.n_terms = 1;
+    E.n_comp = (mode & MAD_ENERGY) ? std::max((int)m.comp_off.size() - 1, 1) : 0;
+    E.batched = m.batched ? 1 : 0;
+    E.energy = energy;
+    E.comp_out = sc.comp_energy;
+    E.n_patch = np;
+    E.comp_patch_ptr = p->d_comp_patch_ptr;
     if (rows) {
         // Edge and vertex terms only: the row-owned kernel, which evaluates an edge from both of its rows and
         // needs no accumulation between workgroups. FP32, clamped, against the patch kernel and its gather:
@@ -220,6 +232,7 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
         G.n_gb = p->n_gb;
         G.n_orphan_vert = p->n_orphan_vert;
         G.n_orphan_block = p->n_orphan_block;
+        if (!hvp) G.energy = E;
         MAD_HIP_TRY(launch_gather(G, s));
         if ((mode & MAD_HESS) && p->n_extra > 0)   // blocks of inserted pairs that no term touches
             MAD_HIP_TRY(launch_zero_blocks(hess, p->d_extra_blocks, p->n_extra, d * d, (int)eb, s));
@@ -228,6 +241,7 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
             G.want_hess = 0;
             G.grad = y;
             G.halo_g = sc.halo_y;
+            G.energy = E;
             MAD_HIP_TRY(launch_gather(G, s));
         }
         if (fallback_pass) {
@@ -259,10 +273,10 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
                 std::memcpy(F.terms[ti].prm, t.prm, sizeof(t.prm));
             }
             MAD_HIP_TRY(launch_fallback(F, s));
+            if (scp == nullptr) p->fb_unclean = false;
         }
         if (ev)
             for (size_t k = 4; k < ev->size() - 1; ++k) MAD_HIP_TRY(hipEventRecord((*ev)[k], s));
-        n_partial_terms = 1;
     }
     for (size_t ti = 0; p->scatter != MAD_SCATTER_PATCH && ti < p->terms.size(); ++ti) {
         const Term& t = p->terms[ti];
@@ -307,17 +321,21 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
         }
         if (ev) MAD_HIP_TRY(hipEventRecord((*ev)[3 + ti], s));
     }
-    if (mode & MAD_ENERGY) {
-        const int ncomp = (int)m.comp_off.size() - 1;
-        if (p->scatter == MAD_SCATTER_COLOR)
-            MAD_HIP_TRY(launch_energy_reduce(sc.partial, 1, (int)p->n_color_slots, p->d_color_comp_ptr,
-                                             std::max(ncomp, 1), m.batched, energy, sc.comp_energy, s));
-        else if (rows)
-            MAD_HIP_TRY(launch_energy_reduce(sc.partial, 1, (int)p->n_row_chunks, p->d_row_comp_ptr,
-                                             std::max(ncomp, 1), m.batched, energy, sc.comp_energy, s));
-        else
-            MAD_HIP_TRY(launch_energy_reduce(sc.partial, n_partial_terms, np, p->d_comp_patch_ptr,
-                                             std::max(ncomp, 1), m.batched, energy, sc.comp_energy, s));
+    if (E.n_comp > 0) {
+        if (p->scatter == MAD_SCATTER_PATCH && !rows) {
+            MAD_HIP_TRY(launch_energy_total(E, s));
+        } else {
+            if (rows) {
+                E.n_patch = (int)p->n_row_chunks;
+                E.comp_patch_ptr = p->d_row_comp_ptr;
+            } else if (p->scatter == MAD_SCATTER_COLOR) {
+                E.n_patch = (int)p->n_color_slots;
+                E.comp_patch_ptr = p->d_color_comp_ptr;
+            } else {
+                E.n_terms = (int)p->terms.size();
+            }
+            MAD_HIP_TRY(launch_energy_reduce(E, s));
+        }
     }
     if (ev) MAD_HIP_TRY(hipEventRecord(ev->back(), s));
     return MAD_OK;

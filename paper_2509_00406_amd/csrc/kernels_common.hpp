@@ -156,6 +156,37 @@ __device__ __forceinline__ void block_reduce_store(double v, double* red, double
     if (threadIdx.x == 0) *out = red[0];
 }
 
+// Energy of component c by one workgroup: partial[t * n_patch + p], patches of component c are
+// [comp_patch_ptr[c], comp_patch_ptr[c + 1]). Each lane sums a fixed strided subset in a fixed order, then a fixed tree.
+__device__ __forceinline__ void energy_component(const EnergyArgs& E, int c, double* red) {
+    const int pb = E.comp_patch_ptr[c], pe = E.comp_patch_ptr[c + 1];
+    double acc = 0.0;
+    for (int t = 0; t < E.n_terms; ++t) {
+        const double* pt = E.partial + (int64_t)t * E.n_patch;
+        int i = pb + (int)threadIdx.x;
+        // eight loads in flight, then the additions in the same order as one at a time
+        for (; i + 7 * kBlock < pe; i += 8 * kBlock) {
+            double v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = pt[i + k * kBlock];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc += v[k];
+        }
+        for (; i < pe; i += kBlock) acc += pt[i];
+    }
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int w = kBlock / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        if (E.batched) E.energy[1 + c] = red[0];
+        if (E.n_comp == 1) E.energy[0] = red[0];
+        else E.comp_out[c] = red[0];
+    }
+}
+
 // sum of red[0, kBlock) in a fixed tree order, by the workgroup's first wave (no barrier: the tree's upper two
 // levels are each lane's own four values, the others shuffles); red is already filled and visible
 __device__ __forceinline__ void block_sum_store(const double* red, double* out) {

@@ -179,8 +179,8 @@ hipError_t launch_zero_blocks(void* hess, const int32_t* list, int64_t n, int dd
 }
 
 __global__ void k_zero_counters(int32_t* a, int32_t* b) {
-    if (threadIdx.x == 0 && a) *a = 0;
-    if (threadIdx.x == 1 && b) *b = 0;
+    if (threadIdx.x < 2 && a) a[threadIdx.x] = 0;
+    if (threadIdx.x == 2 && b) *b = 0;
 }
 
 hipError_t launch_zero_counters(int32_t* a, int32_t* b, hipStream_t s) {
@@ -206,40 +206,11 @@ hipError_t launch_fill(void* ptr, int64_t n_elems, int elem_bytes, hipStream_t s
 }
 
 // ---- deterministic FP64 energy reduction (Sec. 5.5 global reduction) ----------------------------
-// partial[t * n_patch + p]; patches of component c are [comp_patch_ptr[c], comp_patch_ptr[c+1]).
-// One workgroup per component: each lane sums a fixed strided subset in a fixed order, then a fixed
-// tree. With several components a second one-workgroup pass sums the component energies the same way.
-__global__ __launch_bounds__(kBlock) void k_energy_comp(const double* partial, int n_terms, int n_patch,
-                                                        const int32_t* comp_patch_ptr, int batched, double* energy,
-                                                        double* comp_out) {
+// One workgroup per component (energy_component); with several components a second one-workgroup pass sums the
+// component energies the same way.
+__global__ __launch_bounds__(kBlock) void k_energy_comp(EnergyArgs E) {
     __shared__ double red[kBlock];
-    const int c = blockIdx.x;
-    const int pb = comp_patch_ptr[c], pe = comp_patch_ptr[c + 1];
-    double acc = 0.0;
-    for (int t = 0; t < n_terms; ++t) {
-        const double* pt = partial + (int64_t)t * n_patch;
-        int i = pb + (int)threadIdx.x;
-        // eight loads in flight, then the additions in the same order as one at a time
-        for (; i + 7 * kBlock < pe; i += 8 * kBlock) {
-            double v[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = pt[i + k * kBlock];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) acc += v[k];
-        }
-        for (; i < pe; i += kBlock) acc += pt[i];
-    }
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        if (batched) energy[1 + c] = red[0];
-        if (gridDim.x == 1) energy[0] = red[0];
-        else comp_out[c] = red[0];
-    }
+    energy_component(E, blockIdx.x, red);
 }
 
 __global__ __launch_bounds__(kBlock) void k_energy_total(const double* comp, int n_comp, double* energy) {
@@ -255,12 +226,14 @@ __global__ __launch_bounds__(kBlock) void k_energy_total(const double* comp, int
     if (threadIdx.x == 0) energy[0] = red[0];
 }
 
-hipError_t launch_energy_reduce(const double* partial, int n_terms, int n_patch, const int32_t* comp_patch_ptr,
-                                int n_comp, bool batched, double* energy, double* comp_scratch, hipStream_t s) {
-    hipLaunchKernelGGL(k_energy_comp, dim3(n_comp), dim3(kBlock), 0, s, partial, n_terms, n_patch, comp_patch_ptr,
-                       batched ? 1 : 0, energy, comp_scratch);
-    if (n_comp > 1) hipLaunchKernelGGL(k_energy_total, dim3(1), dim3(kBlock), 0, s, comp_scratch, n_comp, energy);
+hipError_t launch_energy_total(const EnergyArgs& E, hipStream_t s) {
+    if (E.n_comp > 1) hipLaunchKernelGGL(k_energy_total, dim3(1), dim3(kBlock), 0, s, E.comp_out, E.n_comp, E.energy);
     return hipGetLastError();
+}
+
+hipError_t launch_energy_reduce(const EnergyArgs& E, hipStream_t s) {
+    hipLaunchKernelGGL(k_energy_comp, dim3(E.n_comp), dim3(kBlock), 0, s, E);
+    return launch_energy_total(E, s);
 }
 
 }  // namespace mad

@@ -636,7 +636,14 @@ __global__ __launch_bounds__(kBlock) void k_eval_patch_f64(PatchLaunch L) {
 template <typename T, int D>
 __global__ __launch_bounds__(kBlock) void k_gather(GatherLaunch G) {
     constexpr int DD = D * D;
-    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
+    // the energies, which need nothing of the gather, by workgroups of their own at its front (a launch fewer)
+    if ((int)blockIdx.x < G.energy.n_comp) {
+        __shared__ double red[kBlock];
+        energy_component(G.energy, (int)blockIdx.x, red);
+        return;
+    }
+    const int64_t tid = (int64_t)((int)blockIdx.x - G.energy.n_comp) * kBlock + threadIdx.x;
+    const int64_t stride = (int64_t)((int)gridDim.x - G.energy.n_comp) * kBlock;
     if (G.want_hess) {
         // one shared block per lane: its index lists read once, each halo partial read whole, the sum and its
         // transpose written row by row (the partials are summed in slot order, as for every entry before)
@@ -691,7 +698,8 @@ template <typename T>
 static hipError_t launch_gather_t(const GatherLaunch& G, hipStream_t s) {
     const int64_t work = std::max<int64_t>({(int64_t)G.n_gb, (int64_t)G.n_gv, (int64_t)G.n_orphan_block * G.var_dim *
                                                                               G.var_dim});
-    const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>((work + kBlock - 1) / kBlock, 8192));
+    const int64_t gather = (G.want_grad || G.want_hess) ? std::max<int64_t>(1, (work + kBlock - 1) / kBlock) : 0;
+    const unsigned blocks = (unsigned)(std::min<int64_t>(gather, 8192) + G.energy.n_comp);
     switch (G.var_dim) {
     case 1: hipLaunchKernelGGL((k_gather<T, 1>), dim3(blocks), dim3(kBlock), 0, s, G); break;
     case 2: hipLaunchKernelGGL((k_gather<T, 2>), dim3(blocks), dim3(kBlock), 0, s, G); break;
@@ -702,7 +710,7 @@ static hipError_t launch_gather_t(const GatherLaunch& G, hipStream_t s) {
 }
 
 hipError_t launch_gather(const GatherLaunch& G, hipStream_t s) {
-    if (!G.want_grad && !G.want_hess) return hipSuccess;
+    if (!G.want_grad && !G.want_hess && G.energy.n_comp == 0) return hipSuccess;
     return G.prec == MAD_F32 ? launch_gather_t<float>(G, s) : launch_gather_t<double>(G, s);
 }
 
@@ -778,7 +786,7 @@ __device__ __forceinline__ void fallback_elem(const FallbackLaunch& F, const Fal
 
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_fallback(FallbackLaunch F) {
-    const int queued = *F.fb_count;
+    const int queued = F.fb_count[0];
     const int cnt = min(queued, F.fb_cap);
     // a queue smaller than the number of queued elements dropped some: the evaluation is not valid
     if (queued > F.fb_cap && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(F.flags + 1, kFlagQueueOverflow);
@@ -806,6 +814,13 @@ __global__ __launch_bounds__(kBlock) void k_fallback(FallbackLaunch F) {
         } else {
             if (A.kind == K_DIRICHLET) fallback_elem<TermDirichlet>(F, A, e, grad_done);
         }
+    }
+    // the queue is left empty for the next evaluation: once every workgroup has read its length
+    if (queued > 0) {
+        __syncthreads();
+        if (threadIdx.x == 0 &&
+            atomicInc(reinterpret_cast<unsigned*>(F.fb_count + 1), gridDim.x - 1) == gridDim.x - 1)
+            F.fb_count[0] = 0;
     }
 }
 

@@ -306,6 +306,8 @@ int build_scatter(mad_problem* p, hipStream_t s) {
         p->fb_cap = (int32_t)std::max<int64_t>(total, 1);
         if ((rc = alloc_layout(p, (void**)&p->d_fb_list, sizeof(uint32_t) * (size_t)p->fb_cap)) != MAD_OK) return rc;
         if ((rc = alloc_layout(p, (void**)&p->d_fb_count, 16)) != MAD_OK) return rc;
+        MAD_HIP_TRY(launch_zero_counters(p->d_fb_count, nullptr, s));
+        p->fb_unclean = false;
     }
     MAD_HIP_TRY(hipStreamSynchronize(s));
     return MAD_OK;

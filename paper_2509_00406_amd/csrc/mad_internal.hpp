@@ -178,7 +178,8 @@ struct mad_problem {
     void* d_halo_y = nullptr;             // [halo vertex slots][D] partial Hessian-vector products
     int64_t n_halo_v = 0, n_halo_b = 0;   // halo slots of shared vertices / shared upper blocks
     uint32_t* d_fb_list = nullptr;
-    int32_t* d_fb_count = nullptr;
+    int32_t* d_fb_count = nullptr;    // two words, zero between evaluations (the redo pass clears what it used)
+    bool fb_unclean = false;          // an evaluation ended in an error between its launches
     int32_t fb_cap = 0;
     size_t lds_bytes = 0;
     int32_t max_lv = 0, max_lb = 0;
@@ -398,6 +399,17 @@ hipError_t launch_move_edges(const int32_t* from, int64_t n, const int32_t* map,
                              hipStream_t s);
 
 // sum the halo partials of every shared entry in a fixed order and write it once; zero orphans
+// fixed-order FP64 reduction of the per-patch energies
+struct EnergyArgs {
+    const double* partial;            // [n_terms][n_patch]
+    const int32_t* comp_patch_ptr;    // [n_comp + 1]
+    int n_terms, n_patch, n_comp, batched;
+    double* energy;                   // [0] total, [1 + c] per component where batched
+    double* comp_out;                 // component energies, summed by a second pass where there are several
+};
+hipError_t launch_energy_reduce(const EnergyArgs& E, hipStream_t s);
+hipError_t launch_energy_total(const EnergyArgs& E, hipStream_t s);   // the second pass alone
+
 struct GatherLaunch {
     int prec, var_dim, want_grad, want_hess;
     void* grad;
@@ -408,6 +420,7 @@ struct GatherLaunch {
     const int32_t *gb_ptr, *gb_src, *gb_gidx, *gb_gidxT;
     const int32_t *orphan_vert, *orphan_block;
     int32_t n_gv, n_gb, n_orphan_vert, n_orphan_block;
+    EnergyArgs energy;        // reduced by the launch's first n_comp workgroups (n_comp 0: not asked for)
 };
 hipError_t launch_gather(const GatherLaunch& G, hipStream_t s);
 
@@ -429,7 +442,7 @@ struct FallbackLaunch {
     const int32_t* rowptr;
     const int32_t* colidx;
     const uint32_t* fb_list;
-    const int32_t* fb_count;
+    int32_t* fb_count;      // [0] queued elements, cleared by the last workgroup to have used it; [1] those
     int32_t fb_cap;
     int32_t* flags;
     double eps;
@@ -441,10 +454,8 @@ struct FallbackLaunch {
 };
 hipError_t launch_fallback(const FallbackLaunch& F, hipStream_t s);
 hipError_t launch_fill(void* ptr, int64_t n_elems, int elem_bytes, hipStream_t s);
-// one small kernel that zeroes up to two int32 counters (either may be null)
+// one small kernel that zeroes the redo queue's two words and the patch queue's head (either may be null)
 hipError_t launch_zero_counters(int32_t* a, int32_t* b, hipStream_t s);
-hipError_t launch_energy_reduce(const double* partial, int n_terms, int n_patch, const int32_t* comp_patch_ptr,
-                                int n_comp, bool batched, double* energy, double* comp_scratch, hipStream_t s);
 
 // pattern builder (kernels_pattern.hip)
 struct PatternTerm {
