@@ -354,12 +354,13 @@ static void for_each_of(size_t n, int64_t work, int64_t grain, const std::functi
 // one or two busy waves. Groups never cross a component boundary, so every patch lies in one component; patches
 // are numbered component by component, in the order of the cuts.
 //
-// A face's group is named by the group's first position in P.order; the names change between levels only, so
-// a traversal reads no entry that another thread writes, and the result does not depend on the threads.
+// A face's group is named by the group's first position in P.order. A traversal may read the name of another
+// group's face while that group's thread changes it, but only from one position within that group to another, which is
+// never its own name: the result does not depend on the threads.
 // whole: the groups of P.start are components still in index order.
 static void split_groups(const mad_mesh& m, Patches& P, bool whole,
                          const std::function<int32_t(int32_t, int32_t)>& parts_of) {
-    constexpr int32_t kBands = 16;
+    constexpr int32_t kBands = 16, kAlone = 4096;   // pieces of a band cut; faces of a group cut by one thread
     struct Cut {
         int32_t b, e, parts;
         bool bands, whole;
@@ -379,47 +380,65 @@ static void split_groups(const mad_mesh& m, Patches& P, bool whole,
     };
     for (size_t g = 0; g < ng; ++g)
         add(todo, P.start[g], P.start[g + 1], parts_of((int32_t)g, P.start[g + 1] - P.start[g]), whole);
-    for (int32_t stamp = 1; !todo.empty(); ++stamp) {
-        int64_t faces = 0;
-        for (const Cut& c : todo) faces += c.e - c.b;
-        for_each_of(todo.size(), faces, 8192, [&](size_t k) {
-            // breadth-first order of the group; further pieces follow in the old order
-            const Cut& c = todo[k];
-            int32_t head = c.b, tail = c.b, scan = c.b;
-            int32_t from = P.order[c.whole ? c.b : c.e - 1];
-            for (;;) {
-                mark[from] = stamp;
-                tmp[tail++] = from;
-                while (head < tail) {
-                    const int32_t f = tmp[head++];
-                    for (int32_t q = m.fadj_ptr[f]; q < m.fadj_ptr[f + 1]; ++q) {
-                        const int32_t g = m.fadj[q];
-                        if (name[g] == c.b && mark[g] != stamp) {
-                            mark[g] = stamp;
-                            tmp[tail++] = g;
-                        }
+    auto traverse = [&](const Cut& c, int32_t stamp) {
+        // breadth-first order of the group; further pieces follow in the old order
+        int32_t head = c.b, tail = c.b, scan = c.b;
+        int32_t from = P.order[c.whole ? c.b : c.e - 1];
+        for (;;) {
+            mark[from] = stamp;
+            tmp[tail++] = from;
+            while (head < tail) {
+                const int32_t f = tmp[head++];
+                for (int32_t q = m.fadj_ptr[f]; q < m.fadj_ptr[f + 1]; ++q) {
+                    const int32_t g = m.fadj[q];
+                    if (__atomic_load_n(&name[g], __ATOMIC_RELAXED) == c.b && mark[g] != stamp) {
+                        mark[g] = stamp;
+                        tmp[tail++] = g;
                     }
                 }
-                if (tail == c.e) break;
-                while (mark[P.order[scan]] == stamp) ++scan;
-                from = P.order[scan];
             }
-            std::copy(tmp.begin() + c.b, tmp.begin() + c.e, P.order.begin() + c.b);
-        });
-        for_each_of(todo.size(), faces, 65536, [&](size_t k) {
-            const Cut& c = todo[k];
-            for (int32_t q = 1; q < (c.bands ? kBands : 2); ++q)
-                for (int32_t i = c.at(q); i < c.at(q + 1); ++i) name[P.order[i]] = c.at(q);
-        });
+            if (tail == c.e) break;
+            while (mark[P.order[scan]] == stamp) ++scan;
+            from = P.order[scan];
+        }
+        std::copy(tmp.begin() + c.b, tmp.begin() + c.e, P.order.begin() + c.b);
+        for (int32_t q = 1; q < (c.bands ? kBands : 2); ++q)
+            for (int32_t i = c.at(q); i < c.at(q + 1); ++i) __atomic_store_n(&name[P.order[i]], c.at(q), __ATOMIC_RELAXED);
+    };
+    auto pieces = [&](const Cut& c, std::vector<Cut>& list, std::vector<int32_t>& at) {
+        for (int32_t q = 0; q < (c.bands ? kBands : 2); ++q) {
+            if (q > 0) at.push_back(c.at(q));
+            add(list, c.at(q), c.at(q + 1), c.bands ? c.parts / kBands : q == 0 ? c.parts / 2 : c.parts - c.parts / 2,
+                false);
+        }
+    };
+    // level by level while groups are large, then each remaining group to its end by one thread
+    std::vector<Cut> small;
+    int32_t stamp = 1;
+    for (; !todo.empty(); ++stamp) {
         next.clear();
-        for (const Cut& c : todo)
-            for (int32_t q = 0; q < (c.bands ? kBands : 2); ++q) {
-                if (q > 0) cuts.push_back(c.at(q));
-                add(next, c.at(q), c.at(q + 1), c.bands ? c.parts / kBands : q == 0 ? c.parts / 2 : c.parts - c.parts / 2,
-                    false);
-            }
+        for (const Cut& c : todo) (c.e - c.b > kAlone ? next : small).push_back(c);
+        todo.swap(next);
+        int64_t faces = 0;
+        for (const Cut& c : todo) faces += c.e - c.b;
+        for_each_of(todo.size(), faces, 8192, [&](size_t k) { traverse(todo[k], stamp); });
+        next.clear();
+        for (const Cut& c : todo) pieces(c, next, cuts);
         todo.swap(next);
     }
+    std::vector<std::vector<int32_t>> found(small.size());
+    int64_t faces = 0;
+    for (const Cut& c : small) faces += c.e - c.b;
+    for_each_of(small.size(), faces, 4096, [&](size_t k) {
+        std::vector<Cut> stack{small[k]};
+        for (int32_t own = stamp; !stack.empty(); ++own) {
+            const Cut c = stack.back();
+            stack.pop_back();
+            traverse(c, own);
+            pieces(c, stack, found[k]);
+        }
+    });
+    for (const auto& f : found) cuts.insert(cuts.end(), f.begin(), f.end());
     P.start.insert(P.start.end(), cuts.begin(), cuts.end());
     std::sort(P.start.begin(), P.start.end());
 }
