@@ -41,14 +41,14 @@ sys.path.insert(0, ROOT)
 # workload (FP32 + FP64 VALU wave instructions x 64 lanes, FMA = 2), and its HBM traffic per launch
 # (FETCH_SIZE x 2.00 + WRITE_SIZE x 1.00, factors from a 1 GiB copy), from the rocprofv3 counter
 # passes in profiles/k_eval_patch_f32_shell1024_counters.md. Valid for the kernel as profiled there.
-FLOPS_PER_ELEM = {"f32": 14697.7, "f64": None}
-# traffic by launch (persistent queue / one workgroup per patch) at the default 384-face layout
-TRAFFIC_BYTES = {"f32": {1: 1.1680e9, 0: 1.0358e9}, "f64": None}
-# the same for the 1000^2 cloth step at its default layout (profiles/k_eval_patch_f32_cloth1000_counters.md)
-CLOTH_TRAFFIC_BYTES = {"f32": 0.5685e9, "f64": None}
-# and for the 1001^2 symmetric Dirichlet parameterisation at its default layout (512-face patches, persistent
-# launch; profiles/k_eval_patch_f32_symdir1001_trace_counters.md)
-SYMDIR_TRAFFIC_BYTES = {"f32": 0.3657e9, "f64": None}
+FLOPS_PER_ELEM = {"f32": 8931.8, "f64": None}
+# traffic at the default layout (444-face patches, 4 waves, the dispatcher as the queue)
+TRAFFIC_BYTES = {"f32": 0.9806e9, "f64": None}
+# the same for the 1000^2 cloth step, evaluated by rows (profiles/k_eval_rows_f32_cloth1000_counters.md)
+CLOTH_TRAFFIC_BYTES = {"f32": 0.4545e9, "f64": None}
+# and for the 1001^2 symmetric Dirichlet parameterisation at its default layout (512-face patches;
+# profiles/k_eval_patch_f32_symdir1001_trace_counters.md)
+SYMDIR_TRAFFIC_BYTES = {"f32": 0.3429e9, "f64": None}
 
 # MI355X published peaks used as roofline denominators
 HBM_PEAK_GBS = 8000.0
@@ -74,7 +74,7 @@ def parse():
     ap.add_argument("--patch-faces", type=int, default=0)
     ap.add_argument("--scatter", choices=["patch", "atomic", "color"], default="patch")
     ap.add_argument("--persistent", action="store_true", help="persistent launch (the default for heavy terms)")
-    ap.add_argument("--per-patch", action="store_true", help="one workgroup per patch (the default for light terms)")
+    ap.add_argument("--per-patch", action="store_true", help="one workgroup per patch")
     ap.add_argument("--wg-waves", type=int, choices=[0, 4, 8], default=0,
                     help="patch kernel tile: waves per workgroup (0: the default 4)")
     ap.add_argument("--autotune", action="store_true", help="choose the layout by timing (batched: always)")
@@ -411,7 +411,7 @@ def main():
     n_terms = {"mlp": 1, "cloth": 2, "symdir": 1}.get(args.workload, len(SHELL_TERMS))
     if layout["scatter"] == mad.SCATTER_PATCH:
         dom_name = {"mlp": "k_eval_patch (learned-density chain + clamp + assembly)",
-                    "cloth": "k_eval_patch (springs + inertia fused)",
+                    "cloth": "k_eval_rows (springs + inertia by rows)",
                     "symdir": "k_eval_patch (symmetric Dirichlet, 2x2 blocks)"}.get(args.workload,
                                                                           "k_eval_patch (StVK + bending fused)")
         dom_ms = stage_ms[2] / n_evals
@@ -442,16 +442,15 @@ def main():
         # a 4x4 reduced Hessian per triangle: few operations per byte, so the HBM stream is the roofline
         achieved = step_bytes / (dom_ms * 1e-3) / 1e9
         at_1001 = (args.symdir_n == 1001 and layout["scatter"] == mad.SCATTER_PATCH and layout["patch_faces"] == 512
-                   and layout["persistent"] and layout["wg_waves"] == 4)
+                   and layout["persistent"] != 2 and layout["wg_waves"] == 4)
         roofline = {"bound": "hbm", "kernel": dom_name, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": achieved / HBM_PEAK_GBS,
                     "traffic": SYMDIR_TRAFFIC_BYTES.get(args.precision) if at_1001 else None, "kernel_ms": dom_ms,
                     "alg_bytes_per_launch": step_bytes}
     elif args.workload == "cloth":
-        # springs are cheap (one 3x3 reduced Hessian each): the fused kernel is held to its HBM stream
+        # springs are cheap (a scalar function of the length each): the row kernel is held to its HBM stream
         achieved = step_bytes / (dom_ms * 1e-3) / 1e9
-        at_1000 = (args.cloth_n == 1000 and layout["scatter"] == mad.SCATTER_PATCH and layout["patch_faces"] == 256
-                   and not layout["persistent"] and layout["wg_waves"] == 4)
+        at_1000 = (args.cloth_n == 1000 and layout["scatter"] == mad.SCATTER_PATCH)   # by rows
         roofline = {"bound": "hbm", "kernel": dom_name, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": achieved / HBM_PEAK_GBS,
                     "traffic": CLOTH_TRAFFIC_BYTES.get(args.precision) if at_1000 else None, "kernel_ms": dom_ms,
@@ -460,8 +459,8 @@ def main():
         achieved = fpe * n_elem / (dom_ms * 1e-3) / 1e12
         roofline = {"bound": "alu", "kernel": dom_name, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                     "frac": achieved / peak,
-                    "traffic": ((TRAFFIC_BYTES.get(args.precision) or {}).get(layout["persistent"])
-                                if layout["patch_faces"] == 384 else None),
+                    "traffic": (TRAFFIC_BYTES.get(args.precision)
+                                if layout["patch_faces"] == 444 and layout["persistent"] != 2 else None),
                     "kernel_ms": dom_ms,
                     "flops_per_element": fpe,
                     "frac_of_unpacked_fp32": achieved / VALU_UNPACKED_TFLOPS[args.precision],
@@ -633,7 +632,7 @@ def residual_jacobian(torch, mad, args, prec, stream):
             "ms_gauss_newton_eval": float(np.median(gn_ms)),
             "gauss_newton_elements_per_s": (ne + nv) / (float(np.median(gn_ms)) * 1e-3),
             "note": "edge-length residuals on every edge + positional residuals on every vertex; the Gauss-Newton "
-                    "evaluation assembles J^T r and J^T J through the patch kernel"}
+                    "evaluation assembles J^T r and J^T J through the row kernel"}
 
 
 def cloth_sizes(torch, mad, args, stream):

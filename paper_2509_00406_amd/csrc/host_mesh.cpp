@@ -350,7 +350,7 @@ static void for_each_of(size_t n, int64_t work, int64_t grain, const std::functi
 // last face of its own stretch of the order it was cut from: for a near part or a band an end of the cut, so
 // that the next cut runs across this one. All patches of a component have the same size to within a few faces:
 // growing patches one after another left half of them as fragments between the full ones (1024^2 shell: 9,770
-// patches of 214 faces on average for a target of 384, now 4,800 of 433), and each fragment is a workgroup with
+// patches of 214 faces on average for a target of 384, now 4,930 of 425), and each fragment is a workgroup with
 // one or two busy waves. Groups never cross a component boundary, so every patch lies in one component; patches
 // are numbered component by component, in the order of the cuts.
 //
