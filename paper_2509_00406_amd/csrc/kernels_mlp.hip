@@ -65,10 +65,18 @@ __device__ __forceinline__ void softplus_logistic(float a, float& sp, float& sg)
     sp = fmaxf(a, 0.0f) + l1p;
 }
 
+// The workgroup's place in an order that keeps neighbours on one XCD, whose L2 then holds the part of x (and of the
+// normals) that they share: workgroups go to the XCDs in turn. 708^2 cylinder: normals 11 us and features 3 us less
+// (a pass 684 -> 670); more triangles in flight per vertex changed nothing.
+__device__ __forceinline__ int64_t xcd_block() {
+    const int per = (int)(gridDim.x >> 3), rest8 = (int)(gridDim.x & 7), xcd = (int)(blockIdx.x & 7);
+    return xcd * per + min(xcd, rest8) + (int)(blockIdx.x >> 3);
+}
+
 // ---- vertex normals ------------------------------------------------------------------------------
 __global__ void k_vertex_normals(const double* x, int64_t nv, const int32_t* vf_ptr, const int32_t* vf,
                                  const int32_t* tris, double* normals) {
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t v = xcd_block() * blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x) {
         double n0 = 0.0, n1 = 0.0, n2 = 0.0;
         for (int32_t q = vf_ptr[v]; q < vf_ptr[v + 1]; ++q) {
             const int32_t* t = tris + 3 * (int64_t)vf[q];
@@ -412,7 +420,7 @@ __global__ __launch_bounds__(kHeadWaves * 64) void k_mlp_head(MlpHeadLaunch L) {
 #undef MAD_MFMA
 
 __global__ __launch_bounds__(256) void k_mlp_features(MlpHeadLaunch L) {
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < L.n; e += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t e = xcd_block() * blockDim.x + threadIdx.x; e < L.n; e += (int64_t)gridDim.x * blockDim.x) {
         double z[6];
         features_at(L, e, z);
 #pragma unroll
