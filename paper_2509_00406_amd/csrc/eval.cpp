@@ -28,8 +28,16 @@ EvalScratch own_scratch(const mad_problem* p) {
     return sc;
 }
 
-int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy, void* grad, void* hess,
-                 hipStream_t s, const double* v, void* y, const EvalScratch* scp) {
+// whether the stream is being recorded into a graph (what is launched then runs later, or never)
+static bool recording(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+static int launch_eval(mad_problem* p, const double* x, uint32_t mode, double* energy, void* grad, void* hess,
+                       hipStream_t s, const double* v, void* y, const EvalScratch* scp) {
     const EvalScratch sc = scp ? *scp : own_scratch(p);
     const bool hvp = v != nullptr;
     const mad_mesh& m = *p->mesh;
@@ -65,7 +73,8 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
                        (p->persistent == 2 || (p->persistent == 1 && p->prec == MAD_F64 && d == 3 && kmode >= 2));
     // The patch queue's head and, in the shared static scratch, the FP64 redo queue's words are cleared by a small
     // kernel. A problem's own redo queue is empty between evaluations: the redo pass clears what it used
-    // (a launch fewer, 4 us), unless an evaluation ended in an error before it.
+    // (a launch fewer, 4 us), unless an evaluation ended in an error before it (eval_problem clears it then, so that
+    // a graph recorded earlier finds it empty too) and that failed as well, or has only been recorded.
     const bool clear_fb = fallback_pass && (scp != nullptr || p->fb_unclean);
     MAD_HIP_TRY(launch_zero_counters(clear_fb ? sc.fb_count : nullptr, queue ? sc.work_counter : nullptr, s));
     if (fallback_pass && scp == nullptr) p->fb_unclean = true;
@@ -273,7 +282,7 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
                 std::memcpy(F.terms[ti].prm, t.prm, sizeof(t.prm));
             }
             MAD_HIP_TRY(launch_fallback(F, s));
-            if (scp == nullptr) p->fb_unclean = false;
+            if (scp == nullptr) p->fb_unclean = clear_fb && recording(s);
         }
         if (ev)
             for (size_t k = 4; k < ev->size() - 1; ++k) MAD_HIP_TRY(hipEventRecord((*ev)[k], s));
@@ -339,6 +348,14 @@ int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy,
     }
     if (ev) MAD_HIP_TRY(hipEventRecord(ev->back(), s));
     return MAD_OK;
+}
+
+int eval_problem(mad_problem* p, const double* x, uint32_t mode, double* energy, void* grad, void* hess,
+                 hipStream_t s, const double* v, void* y, const EvalScratch* scp) {
+    const int rc = launch_eval(p, x, mode, energy, grad, hess, s, v, y, scp);
+    if (rc != MAD_OK && scp == nullptr && p->fb_unclean)
+        p->fb_unclean = launch_zero_counters(p->d_fb_count, nullptr, s) != hipSuccess || recording(s);
+    return rc;
 }
 
 }  // namespace mad
