@@ -249,8 +249,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                 }
             }
             esum += row <= col ? P.f : 0.0;
+            // positions count where a term reads them: a vertex on no edge may hold anything
+            const bool read = is_edge ? L.n_edge > 0 : dia && L.n_vert > 0;
             bad = bad || !finite(P.f) || !finite(fabs(P.g[0]) + fabs(P.g[1]) + fabs(P.g[2]) + fabs(P.along) + fabs(P.across)) ||
-                  !finite(xr[0]) || !finite(xr[1]) || !finite(xr[2]);
+                  (read && (!finite(xr[0]) || !finite(xr[1]) || !finite(xr[2])));
             // the row's own part of the element: gradient, and diagonal block or product
             T* to = part + lane * kRowComps;
             if constexpr (MODE >= 1) {
