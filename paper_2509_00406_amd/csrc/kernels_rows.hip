@@ -25,76 +25,106 @@ namespace {
 constexpr int kRowWaves = kBlock / 64;
 constexpr int kRowComps = 9;   // diagonal block (upper half: 6 in 3D) or product (3), then the gradient (3)
 
-// An edge term is a function of the edge's length l: its gradient lies along the edge's unit vector u and its
-// Hessian is along u u^T + across (I - u u^T). The derivatives are forward mode over the edge's own axes,
-// where the two coordinates across it vanish (element.hpp). Terms add up as these numbers.
-// A vertex term is a quadratic with an isotropic Hessian (along = across).
-template <typename T>
+// The contributions of a lane's terms, which add up. Energy, gradient and the unclamped Hessian are the caller's
+// axes' own derivatives. (Through the edge's axes, below, the unclamped Hessian of a 200^2 cloth was 1.2 times as far from
+// 64 bits in FP32 and 1.8 times in FP64.)
+// Clamped: an edge term is a function of the edge's length l, so its Hessian is along u u^T + across (I - u u^T)
+// with the edge's unit vector u, from forward mode over the edge's own axes, where the two coordinates across it
+// vanish (element.hpp). A vertex term is a quadratic with an isotropic Hessian (along = across).
+template <typename T, int MODE>
 struct RowPart {
     double f;
-    T g[3], along, across;   // g: gradient at the column's vertex
+    T g[3];              // gradient at the column's vertex
+    T along, across;     // clamped
 };
+template <typename T>
+struct RowPart<T, 2> {
+    double f;
+    T g[3], h[6];
+};
+template <typename T, int MODE>
+__device__ __forceinline__ T hess_size(const RowPart<T, MODE>& P) {
+    if constexpr (MODE == 2) return fabs(P.h[0]) + fabs(P.h[1]) + fabs(P.h[2]) + fabs(P.h[3]) + fabs(P.h[4]) + fabs(P.h[5]);
+    else return fabs(P.along) + fabs(P.across);
+}
 
 template <class Term, typename T, int MODE>
 __device__ __forceinline__ void add_edge(const RowTerm& A, const double (&in)[4], const double (&r)[3], double l,
-                                         const T (&u)[3], double il, T te, RowPart<T>& P) {
-    static_assert(Term::NREST <= 2 && Term::NS == 2 && Term::FRAME == 3, "an edge term");
+                                         double il, T te, RowPart<T, MODE>& P) {
+    static_assert(Term::NREST <= 2 && Term::NS == 2 && Term::FRAME == 3 && Term::NRES <= 1, "an edge term");
     const double rest[2] = {in[0], in[1]};
-    T h0 = T(0), h1 = T(0);
     if constexpr (MODE == 0) {
         P.f += Term::template energy<double>(r, rest, A.prm);
         return;
-    }
-    if constexpr (sizeof(T) == 8) {
-        // energy and gradient in the caller's axes: neighbouring edges' cancel, and the rounding of l would show
+    } else if constexpr (MODE == 3 && sizeof(T) == 4) {
+        // along the edge in FP64, rounded once: no less exact, and in fewer registers than FP32 duals of three
+        P.f += Term::template energy<double>(r, rest, A.prm);
+        using S = D1<3, double>;
+        const S q[3] = {var<S>(0, l), var<S>(1, 0.0), var<S>(2, 0.0)};
+        const double gl = Term::template energy<S>(q, rest, A.prm).g[0] * il;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) P.g[c] += T(gl * r[c]);
+    } else if constexpr (Term::NRES > 0) {
         using S = D1<3, T>;
+        const S q[3] = {var<S>(0, r[0]), var<S>(1, r[1]), var<S>(2, r[2])};
+        S res[1];
+        Term::template residual<S>(q, rest, A.prm, res);
+        P.f += 0.5 * res[0].v * res[0].v;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            P.g[a] += T(res[0].v) * res[0].g[a];
+            if constexpr (MODE == 2)
+#pragma unroll
+                for (int b = a; b < 3; ++b) P.h[Packed<3>::at(a, b)] += res[0].g[a] * res[0].g[b];
+        }
+    } else {
+        using S = typename std::conditional<MODE == 2, HD<3, T>, D1<3, T>>::type;
         const S q[3] = {var<S>(0, r[0]), var<S>(1, r[1]), var<S>(2, r[2])};
         const S f = Term::template energy<S>(q, rest, A.prm);
         P.f += f.v;
 #pragma unroll
         for (int c = 0; c < 3; ++c) P.g[c] += f.g[c];
-        if constexpr (MODE == 1) return;
+        if constexpr (MODE == 2)
+#pragma unroll
+            for (int k = 0; k < 6; ++k) P.h[k] += f.h[k];
     }
-    double fl = 0.0;
-    T gu = T(0);
-    if constexpr (Term::NRES > 0) {
-        using S = D1<3, T>;
-        const S q[3] = {var<S>(0, l), var<S>(1, 0.0), var<S>(2, 0.0)};
-        S res[1];
-        Term::template residual<S>(q, rest, A.prm, res);
-        fl = 0.5 * res[0].v * res[0].v;
-        gu = T(res[0].v) * res[0].g[0];
-        h0 = res[0].g[0] * res[0].g[0];
-        h1 = res[0].g[1] * res[0].g[1];
-    } else {
-        using S = typename std::conditional<MODE == 1, D1<3, T>, HD<3, T>>::type;
-        const S q[3] = {var<S>(0, l), var<S>(1, 0.0), var<S>(2, 0.0)};
-        const S f = Term::template energy<S>(q, rest, A.prm);
-        fl = f.v;
-        gu = f.g[0];
-        if constexpr (MODE >= 2) {
+    if constexpr (MODE == 3) {
+        T h0, h1;
+        if constexpr (Term::NRES > 0) {
+            using S = D1<3, T>;
+            const S q[3] = {var<S>(0, l), var<S>(1, 0.0), var<S>(2, 0.0)};
+            S res[1];
+            Term::template residual<S>(q, rest, A.prm, res);
+            h0 = res[0].g[0] * res[0].g[0];
+            h1 = res[0].g[1] * res[0].g[1];
+        } else {
+            using S = HD<3, T>;
+            const S q[3] = {var<S>(0, l), var<S>(1, 0.0), var<S>(2, 0.0)};
+            const S f = Term::template energy<S>(q, rest, A.prm);
             h0 = f.h[Packed<3>::at(0, 0)];
             h1 = f.h[Packed<3>::at(1, 1)];
         }
-    }
-    if constexpr (sizeof(T) == 4) {
-        P.f += fl;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) P.g[c] += T((double)gu * (r[c] * il));
-    }
-    if constexpr (MODE == 3) {
         // clamped in the orthonormal coordinate (x_1 - x_0) / sqrt(2), whose Hessian is twice this one; the
         // floor of the translations is added where the blocks are formed
-        h0 = T(0.5) * fmax(T(2) * h0, te);
-        h1 = T(0.5) * fmax(T(2) * h1, te);
+        P.along += T(0.5) * fmax(T(2) * h0, te);
+        P.across += T(0.5) * fmax(T(2) * h1, te);
     }
-    P.along += h0;
-    P.across += h1;
+}
+
+template <typename T, int MODE>
+__device__ __forceinline__ void add_isotropic(RowPart<T, MODE>& P, T h, T te) {
+    if constexpr (MODE == 2) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) P.h[Packed<3>::at(c, c)] += h;
+    } else if constexpr (MODE == 3) {
+        P.along += fmax(h, te);
+        P.across += fmax(h, te);
+    }
 }
 
 template <class Term, typename T, int MODE>
 __device__ __forceinline__ void add_vertex(const RowTerm& A, const double (&in)[4], const double (&x)[3], T te,
-                                           RowPart<T>& P) {
+                                           RowPart<T, MODE>& P) {
     static_assert(Term::NVD == 4 && Term::NS == 1 && Term::NREST == 0, "a vertex term");
     if constexpr (MODE == 0) {
         P.f += Term::template energy<double>(x, in, A.prm);
@@ -112,9 +142,7 @@ __device__ __forceinline__ void add_vertex(const RowTerm& A, const double (&in)[
             for (int c = 0; c < 3; ++c) P.g[c] += T(res[m].v) * res[m].g[c];
             h += res[m].g[0] * res[m].g[0];
         }
-        h = MODE == 3 ? fmax(h, te) : h;
-        P.along += h;
-        P.across += h;
+        add_isotropic<T, MODE>(P, h, te);
     } else {
         using S = typename std::conditional<MODE == 1, D1<3, T>, HD<3, T>>::type;
         const S q[3] = {var<S>(0, x[0]), var<S>(1, x[1]), var<S>(2, x[2])};
@@ -122,11 +150,7 @@ __device__ __forceinline__ void add_vertex(const RowTerm& A, const double (&in)[
         P.f += f.v;
 #pragma unroll
         for (int c = 0; c < 3; ++c) P.g[c] += f.g[c];
-        if constexpr (MODE >= 2) {
-            const T h = MODE == 3 ? fmax(f.h[0], te) : f.h[0];
-            P.along += h;
-            P.across += h;
-        }
+        if constexpr (MODE >= 2) add_isotropic<T, MODE>(P, f.h[0], te);
     }
 }
 
@@ -140,7 +164,8 @@ __device__ __forceinline__ void vertex_inputs(const RowTerm& A, int row, double 
     for (int k = 0; k < 4; ++k) in[k] = A.vdata[(int64_t)row * 4 + k];
 }
 
-template <typename T, int MODE>
+// HVP: the matrix-free product instead of the blocks (modes 2 and 3)
+template <typename T, int MODE, bool HVP>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 3))) void k_eval_rows(RowLaunch L) {
     __shared__ __align__(16) T s_part[kRowWaves][64 * kRowComps];   // the lanes' contributions, then the unit's blocks
     __shared__ T s_sum[kRowWaves][64 * kRowComps];    // the rows' sums
@@ -223,20 +248,25 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
             }
             if (dia && L.n_vert > 0) vertex_inputs(L.verts[0], row, in);
             if (p0 == 0 && more) fetch_lanes(next_at, next_to, next_col, next_edge, next_start);
-            RowPart<T> P{};
-            T d[3] = {T(0), T(0), T(0)}, fl = T(0);   // u; floor of the translations, summed over the edge terms
+            RowPart<T, MODE> P{};
+            T d[3] = {T(0), T(0), T(0)}, fl = T(0);   // clamped: u; floor of the translations, summed over the edge terms
             if (is_edge) {
                 double r[3];   // from the row's vertex to the column's
 #pragma unroll
                 for (int c = 0; c < 3; ++c) r[c] = xc[c] - xr[c];
-                const double rr = dot3(r, r), il = rr > 0.0 ? frsq(rr) : 0.0, l = length_of(rr, il);
+                double l = 0.0, il = 0.0;
+                if constexpr (MODE == 3) {
+                    const double rr = dot3(r, r);
+                    il = rr > 0.0 ? frsq(rr) : 0.0;
+                    l = length_of(rr, il);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) d[c] = rr > 0.0 ? T(r[c] * il) : T(c == 0 ? 1 : 0);
+                    for (int c = 0; c < 3; ++c) d[c] = rr > 0.0 ? T(r[c] * il) : T(c == 0 ? 1 : 0);
+                }
                 for (int t = 0; t < L.n_edge;) {
                     const RowTerm& A = L.edges[t];
-                    if (A.kind == K_SPRING) add_edge<TermSpring, T, MODE>(A, in, r, l, d, il, te, P);
-                    else if (A.kind == K_RES_EDGE) add_edge<TermResEdge, T, MODE>(A, in, r, l, d, il, te, P);
-                    else add_edge<TermEdgeSqlen, T, MODE>(A, in, r, l, d, il, te, P);
+                    if (A.kind == K_SPRING) add_edge<TermSpring, T, MODE>(A, in, r, l, il, te, P);
+                    else if (A.kind == K_RES_EDGE) add_edge<TermResEdge, T, MODE>(A, in, r, l, il, te, P);
+                    else add_edge<TermEdgeSqlen, T, MODE>(A, in, r, l, il, te, P);
                     if (MODE == 3) fl += T(0.5) * te;
                     if (++t < L.n_edge) edge_inputs(L.edges[t], edge, in);
                 }
@@ -249,10 +279,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                 }
             }
             esum += row <= col ? P.f : 0.0;
-            // positions count where a term reads them: a vertex on no edge may hold anything
-            const bool read = is_edge ? L.n_edge > 0 : dia && L.n_vert > 0;
-            bad = bad || !finite(P.f) || !finite(fabs(P.g[0]) + fabs(P.g[1]) + fabs(P.g[2]) + fabs(P.along) + fabs(P.across)) ||
-                  (read && (!finite(xr[0]) || !finite(xr[1]) || !finite(xr[2])));
+            // a position that is not finite shows in the energy of every term that reads it (and a vertex that no
+            // term reads may hold anything)
+            bad = bad || !finite(P.f) || !finite(fabs(P.g[0]) + fabs(P.g[1]) + fabs(P.g[2]) + hess_size<T, MODE>(P));
             // the row's own part of the element: gradient, and diagonal block or product
             T* to = part + lane * kRowComps;
             if constexpr (MODE >= 1) {
@@ -261,25 +290,33 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                     for (int c = 0; c < 3; ++c) to[6 + c] = dia ? P.g[c] : -P.g[c];
             }
             if constexpr (MODE >= 2) {
-                if (have && L.hvp) {
-                    T vr[3], vc[3], along = T(0);
+                if (have) {
+                    if constexpr (HVP) {
+                        T v[3], w[3], along = T(0);   // of the row's vertex; less the column's
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        vr[c] = T(L.v[(int64_t)row * 3 + c]);
-                        vc[c] = dia ? T(0) : T(L.v[(int64_t)col * 3 + c]);
-                        along += d[c] * (vr[c] - vc[c]);
+                        for (int c = 0; c < 3; ++c) {
+                            v[c] = T(L.v[(int64_t)row * 3 + c]);
+                            w[c] = v[c] - (dia ? T(0) : T(L.v[(int64_t)col * 3 + c]));
+                            along += d[c] * w[c];
+                        }
+                        if constexpr (MODE == 3) along *= P.along - P.across;
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            if constexpr (MODE == 2)
+                                to[a] = P.h[Packed<3>::at(a, 0)] * w[0] + P.h[Packed<3>::at(a, 1)] * w[1] + P.h[Packed<3>::at(a, 2)] * w[2];
+                            else
+                                to[a] = P.across * w[a] + along * d[a] + fl * (T(2) * v[a] - w[a]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int a = 0; a < 3; ++a)
+#pragma unroll
+                            for (int b = a; b < 3; ++b) {
+                                const int k = Packed<3>::at(a, b);
+                                if constexpr (MODE == 2) to[k] = P.h[k];
+                                else to[k] = (P.along - P.across) * d[a] * d[b] + (a == b ? P.across + fl : T(0));
+                            }
                     }
-                    along *= P.along - P.across;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c)
-                        to[c] = P.across * (vr[c] - vc[c]) + along * d[c] + fl * (vr[c] + vc[c]);
-                } else if (have) {
-#pragma unroll
-                    for (int a = 0; a < 3; ++a)
-#pragma unroll
-                        for (int b = a; b < 3; ++b)
-                            to[Packed<3>::at(a, b)] =
-                                (P.along - P.across) * d[a] * d[b] + (a == b ? P.across + fl : T(0));
                 }
             }
             if constexpr (MODE >= 1) {
@@ -302,14 +339,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                     }
                 };
                 if constexpr (MODE >= 2) {
-                    if (L.hvp) row_sums(std::integral_constant<int, 3>{}, T(0), 0);
+                    if constexpr (HVP) row_sums(std::integral_constant<int, 3>{}, T(0), 0);
                     else row_sums(std::integral_constant<int, 6>{}, T(0), 0);
                 }
                 if (L.want_grad) row_sums(std::integral_constant<int, 3>{}, 0.0, 6);
                 wave_sync();
             }
             if constexpr (MODE >= 2) {
-                if (!L.hvp) {
+                if constexpr (!HVP) {
                     T* H = static_cast<T*>(L.hess) + (int64_t)(k0 + p0) * 9;
                     if (have) {
                         const T* q = sum + i * kRowComps;
@@ -318,7 +355,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                         for (int a = 0; a < 3; ++a)
 #pragma unroll
                             for (int b = 0; b < 3; ++b) {
-                                const T o = (P.across - P.along) * d[a] * d[b] + (a == b ? fl - P.across : T(0));
+                                T o;
+                                if constexpr (MODE == 2) o = -P.h[Packed<3>::at(a, b)];
+                                else o = (P.across - P.along) * d[a] * d[b] + (a == b ? fl - P.across : T(0));
                                 blk[3 * a + b] = dia ? q[Packed<3>::at(a, b)] : o;
                             }
                         if (single) {
@@ -341,15 +380,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
         }
         wave_sync();
         if constexpr (MODE >= 2) {
-            if (!single && !L.hvp)
+            if constexpr (HVP) {
+                for (int k = lane; k < nrows * 3; k += 64)
+                    static_cast<T*>(L.y)[(int64_t)row0 * 3 + k] = sum[(k / 3) * kRowComps + k % 3];
+            } else if (!single) {
                 for (int k = lane; k < nrows * 9; k += 64) {
                     const int j = k / 9, q = k - j * 9;
                     static_cast<T*>(L.hess)[(int64_t)s_dia[w][j] * 9 + q] =
                         sum[j * kRowComps + Packed<3>::at(q / 3, q % 3)];
                 }
-            if (L.hvp)
-                for (int k = lane; k < nrows * 3; k += 64)
-                    static_cast<T*>(L.y)[(int64_t)row0 * 3 + k] = sum[(k / 3) * kRowComps + k % 3];
+            }
         }
         if constexpr (MODE >= 1) {
             if (L.want_grad)
@@ -379,10 +419,16 @@ template <typename T>
 hipError_t launch_rows(const RowLaunch& L, hipStream_t s) {
     const dim3 grid(L.n_chunks), block(kBlock);
     switch (L.mode) {
-    case 0: hipLaunchKernelGGL((k_eval_rows<T, 0>), grid, block, 0, s, L); break;
-    case 1: hipLaunchKernelGGL((k_eval_rows<T, 1>), grid, block, 0, s, L); break;
-    case 2: hipLaunchKernelGGL((k_eval_rows<T, 2>), grid, block, 0, s, L); break;
-    case 3: hipLaunchKernelGGL((k_eval_rows<T, 3>), grid, block, 0, s, L); break;
+    case 0: hipLaunchKernelGGL((k_eval_rows<T, 0, false>), grid, block, 0, s, L); break;
+    case 1: hipLaunchKernelGGL((k_eval_rows<T, 1, false>), grid, block, 0, s, L); break;
+    case 2:
+        if (L.hvp) hipLaunchKernelGGL((k_eval_rows<T, 2, true>), grid, block, 0, s, L);
+        else hipLaunchKernelGGL((k_eval_rows<T, 2, false>), grid, block, 0, s, L);
+        break;
+    case 3:
+        if (L.hvp) hipLaunchKernelGGL((k_eval_rows<T, 3, true>), grid, block, 0, s, L);
+        else hipLaunchKernelGGL((k_eval_rows<T, 3, false>), grid, block, 0, s, L);
+        break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
