@@ -23,7 +23,11 @@ namespace mad {
 namespace {
 
 constexpr int kRowWaves = kBlock / 64;
-constexpr int kRowComps = 9;   // diagonal block (upper half: 6 in 3D) or product (3), then the gradient (3)
+// What a lane leaves in LDS for its row: the diagonal block (upper half: 6 in 3D) or the product (3), then the gradient
+// (3); an odd stride. Gradients alone take a third of a Hessian's LDS, so that it does not limit the waves (FP64
+// gradient of a 1000^2 cloth 95 -> 87 us; through patches 89).
+constexpr int row_comps(int mode, bool hvp) { return mode >= 2 ? (hvp ? 7 : 9) : mode == 1 ? 3 : 1; }
+constexpr int row_grad(int mode, bool hvp) { return mode >= 2 ? (hvp ? 3 : 6) : 0; }
 
 // The contributions of a lane's terms, which add up. Energy, gradient and the unclamped Hessian are the caller's
 // axes' own derivatives. (Through the edge's axes, below, the unclamped Hessian of a 200^2 cloth was 1.2 times as far from
@@ -167,6 +171,7 @@ __device__ __forceinline__ void vertex_inputs(const RowTerm& A, int row, double 
 // HVP: the matrix-free product instead of the blocks (modes 2 and 3)
 template <typename T, int MODE, bool HVP>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 3))) void k_eval_rows(RowLaunch L) {
+    constexpr int kRowComps = row_comps(MODE, HVP), kGrad = row_grad(MODE, HVP);
     __shared__ __align__(16) T s_part[kRowWaves][64 * kRowComps];   // the lanes' contributions, then the unit's blocks
     __shared__ T s_sum[kRowWaves][64 * kRowComps];    // the rows' sums
     __shared__ int s_off[kRowWaves][65];              // first block of each row, from the unit's first
@@ -287,7 +292,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
             if constexpr (MODE >= 1) {
                 if (have && L.want_grad)
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) to[6 + c] = dia ? P.g[c] : -P.g[c];
+                    for (int c = 0; c < 3; ++c) to[kGrad + c] = dia ? P.g[c] : -P.g[c];
             }
             if constexpr (MODE >= 2) {
                 if (have) {
@@ -342,7 +347,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                     if constexpr (HVP) row_sums(std::integral_constant<int, 3>{}, T(0), 0);
                     else row_sums(std::integral_constant<int, 6>{}, T(0), 0);
                 }
-                if (L.want_grad) row_sums(std::integral_constant<int, 3>{}, 0.0, 6);
+                if (L.want_grad) row_sums(std::integral_constant<int, 3>{}, 0.0, kGrad);
                 wave_sync();
             }
             if constexpr (MODE >= 2) {
@@ -394,7 +399,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
         if constexpr (MODE >= 1) {
             if (L.want_grad)
                 for (int k = lane; k < nrows * 3; k += 64)
-                    static_cast<T*>(L.grad)[(int64_t)row0 * 3 + k] = sum[(k / 3) * kRowComps + 6 + k % 3];
+                    static_cast<T*>(L.grad)[(int64_t)row0 * 3 + k] = sum[(k / 3) * kRowComps + kGrad + k % 3];
         }
         wave_sync();   // the sums are read before the next unit writes them
         at = next_at;
