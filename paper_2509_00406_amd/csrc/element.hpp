@@ -194,15 +194,16 @@ __device__ __forceinline__ double least_normal(double) { return 2.22507385850720
 //
 // Scaled rotations (the idea of the fast Givens transformation of W. M. Gentleman, 1973, and
 // S. Hammarling, 1974, applied to Jacobi rotations): the off-diagonal entries and the eigenvector
-// columns are kept with a diagonal scale, 2 a_ij = d_i d_j b_ij (i != j) and V = W diag(d) / sqrt(2), while the
+// columns are kept with a diagonal scale, 2 a_ij = d_i d_j b_ij (i != j) and V = W diag(d), while the
 // diagonal of A is kept as is. A rotation in the (p, q) plane multiplies d_p and d_q by c; the stored entries then
 // change by one fused multiply-add each, b_ip -= t (d_q / d_p) b_iq and b_iq += t (d_p / d_q) b_ip (the same for
 // W's columns), where the plain rotation needs two products and a multiply-add. With e = 1/d^2 carried along
-// (e <- e (1 + t^2)) the two factors are t d_p d_q times e_p and e_q, so no division is needed; the sqrt(2)
-// that d starts with makes d_p d_q b_pq = 2 a_pq, which is what t and the diagonal take. c >= 1/sqrt(2), so
-// after s sweeps d >= 2^(1/2 - s (N - 1) / 2): no underflow in FP32 within the sweep limit, and the
+// (e <- e (1 + t^2)) the two factors are t d_p d_q times e_p and e_q, so no division is needed; the off-diagonal
+// entries are doubled once, exactly, since 2 a_pq is what t and the diagonal take (scales that start at sqrt(2)
+// instead, which FP32 rounds, made a diagonal matrix come out 6e-8 too small). c >= 1/sqrt(2), so
+// after s sweeps d >= 2^(-s (N - 1) / 2): no underflow in FP32 within the sweep limit, and the
 // stored entries grow by at most the inverse.
-// On return A's diagonal holds the eigenvalues and W diag(d) / sqrt(2) the eigenvectors. The matrix is
+// On return A's diagonal holds the eigenvalues and W diag(d) the eigenvectors. The matrix is
 // scaled to max |a_ij| = 1 first (and the eigenvalues scaled back) so squares cannot overflow.
 // Returns whether the off-diagonal mass fell below tol of the Frobenius norm within max_sweeps.
 __host__ __device__ constexpr int rr_players(int n) { return n + (n & 1); }
@@ -286,8 +287,8 @@ __device__ __forceinline__ bool jacobi_eig(T (&A)[Packed<N>::N], T (&W)[N][N], T
     T inv[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        dsc[i] = T(1.4142135623730951);
-        inv[i] = T(0.5);
+        dsc[i] = T(1);
+        inv[i] = T(1);
 #pragma unroll
         for (int j = 0; j < N; ++j) W[i][j] = (i == j) ? T(1) : T(0);
     }
@@ -296,7 +297,9 @@ __device__ __forceinline__ bool jacobi_eig(T (&A)[Packed<N>::N], T (&W)[N][N], T
     for (int i = 0; i < Packed<N>::N; ++i) amax = fmax(amax, fabs(A[i]));
     const T scale = amax > T(0) ? frcp(amax) : T(1);
 #pragma unroll
-    for (int i = 0; i < Packed<N>::N; ++i) A[i] *= scale;
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = i; j < N; ++j) A[Packed<N>::at(i, j)] *= i == j ? scale : T(2) * scale;
     bool conv = jacobi_converged<N, T>(A, dsc, tol);
     if (!conv && max_sweeps > 0) {
         // the first sweep on its own: W is still the identity and the scales one there, so the
@@ -752,7 +755,7 @@ __device__ __forceinline__ void element_derivs(const double* xs, const double* r
     }
 }
 
-// C = U diag(max(lambda, floor)) U^T (U = V diag(dsc) / sqrt(2)) of the symmetric N x N matrix A; returns whether the
+// C = U diag(max(lambda, floor)) U^T (U = V diag(dsc)) of the symmetric N x N matrix A; returns whether the
 // eigen-decomposition converged
 template <int N, typename T>
 __device__ __forceinline__ bool clamp_matrix(T (&A)[Packed<N>::N], T te, T (&C)[Packed<N>::N]) {
@@ -762,9 +765,9 @@ __device__ __forceinline__ bool clamp_matrix(T (&A)[Packed<N>::N], T te, T (&C)[
     for (int i = 0; i < Packed<N>::N; ++i) C[i] = T(0);
 #pragma unroll
     for (int m = 0; m < N; ++m) {
-        // eigenvector m is column m of V times dsc[m] / sqrt(2): its scale squared goes with the eigenvalue
+        // eigenvector m is column m of V times dsc[m]: its scale squared goes with the eigenvalue
         const T lam = A[Packed<N>::at(m, m)];
-        const T lp = (lam > te ? lam : te) * (T(0.5) * dsc[m] * dsc[m]);
+        const T lp = (lam > te ? lam : te) * (dsc[m] * dsc[m]);
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const T li = lp * V[i][m];
