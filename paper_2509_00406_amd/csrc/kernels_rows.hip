@@ -12,10 +12,11 @@
 // through LDS in the order of memory (a unit's blocks are one contiguous range).
 //
 // 1000^2 cloth (2,996,001 springs, 1,000,000 vertex terms, FP32, clamped): 175 us on inputs that no cache holds
-// (140 us on warm ones) where the patch kernel took 344 and its gather 26; it moves 162 MB in and 280 MB out of
+// (130 us on warm ones) where the patch kernel took 344 and its gather 26; it moves 162 MB in and 280 MB out of
 // the 392 MB that it cannot do without, 2.5 TB/s. Each unit's columns are loaded while the unit before it is worked
 // on, and the row sums keep eight LDS reads in flight (189 -> 179 us); five waves per SIMD (96 registers) against
-// four 200 -> 179 us, six spill.
+// four 200 -> 179 us, six spill. Two spilled registers cost 8% (190 us), so a unit's table entry, which all lanes
+// hold alike, moves to scalar registers as soon as it has arrived.
 #include "kernels_common.hpp"
 
 namespace mad {
@@ -168,6 +169,10 @@ __device__ __forceinline__ void vertex_inputs(const RowTerm& A, int row, double 
     for (int k = 0; k < 4; ++k) in[k] = A.vdata[(int64_t)row * 4 + k];
 }
 
+__device__ __forceinline__ int2 uniform2(int2 v) {
+    return int2{__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y)};
+}
+
 // HVP: the matrix-free product instead of the blocks (modes 2 and 3)
 template <typename T, int MODE, bool HVP>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 3))) void k_eval_rows(RowLaunch L) {
@@ -214,7 +219,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
         const int k0 = __builtin_amdgcn_readfirstlane(at.y), nb = __builtin_amdgcn_readfirstlane(to_at.y) - k0;
         const bool single = nb <= 64;
         int2 next_at{0, 0}, next_to{0, 0};
-        const bool more = u + kRowWaves < u_end;
+        const bool more = __builtin_amdgcn_readfirstlane(u + kRowWaves) < u_end;
         if (more) fetch_unit(u + kRowWaves, next_at, next_to);
         if (lane < nrows) off[lane] = start_l;
         if (lane == 0) off[nrows] = nb;
@@ -252,7 +257,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
                 for (int c = 0; c < 3; ++c) xr[c] = L.x[(int64_t)row * 3 + c];
             }
             if (dia && L.n_vert > 0) vertex_inputs(L.verts[0], row, in);
-            if (p0 == 0 && more) fetch_lanes(next_at, next_to, next_col, next_edge, next_start);
+            if (p0 == 0 && more) {
+                next_at = uniform2(next_at);
+                next_to = uniform2(next_to);
+                fetch_lanes(next_at, next_to, next_col, next_edge, next_start);
+            }
             RowPart<T, MODE> P{};
             T d[3] = {T(0), T(0), T(0)}, fl = T(0);   // clamped: u; floor of the translations, summed over the edge terms
             if (is_edge) {
