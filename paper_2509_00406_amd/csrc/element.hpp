@@ -423,30 +423,20 @@ __device__ __forceinline__ T helmert_entry(const T (&h)[Packed<Term::KR>::N], in
     return acc;
 }
 
-// Energy and stencil gradient: in FP32 from the derivatives g over the relative coordinates in the axes
-// (u, m, n); in FP64 from first-order duals in the caller's axes (a few per cent of the element's work), since
-// the gradients of neighbouring elements cancel and the rounding of the axes would show.
+// Energy and stencil gradient from first-order duals in the caller's axes, as without the clamp: the gradients of
+// neighbouring elements cancel and the rounding of the element's own axes would show. (FP64 shell gradients 5e-14 instead of
+// 1.3e-14; in FP32 the clamped gradient was 5 to 12% further from 64 bits than the unclamped one, and its FP64 energy 5e-16
+// instead of 5e-17; the duals take 1% of a 1024^2 shell, 1200 -> 1211 us.)
 template <class Term, typename T>
-__device__ __forceinline__ void frame_gradient(double f, const T (&g)[Term::KR], const double (&r)[Term::KR],
-                                               const double* rest, const double* prm, const T (&R)[3][3],
+__device__ __forceinline__ void frame_gradient(const double (&r)[Term::KR], const double* rest, const double* prm,
                                                ElemOut<Term, T>& out) {
-    T gx[Term::KR];
-    if constexpr (sizeof(T) == 8) {
-        using S = D1<Term::KR, T>;
-        S rs[Term::KR];
+    using S = D1<Term::KR, T>;
+    S rs[Term::KR];
 #pragma unroll
-        for (int i = 0; i < Term::KR; ++i) rs[i] = var<S>(i, r[i]);
-        const S q = Term::template energy<S>(rs, rest, prm);
-        out.f = q.v;
-#pragma unroll
-        for (int i = 0; i < Term::KR; ++i) gx[i] = q.g[i];
-    } else {
-        out.f = f;
-#pragma unroll
-        for (int s = 0; s < Term::KR; s += 3)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) gx[s + c] = R[c][0] * g[s] + R[c][1] * g[s + 1] + R[c][2] * g[s + 2];
-    }
+    for (int i = 0; i < Term::KR; ++i) rs[i] = var<S>(i, r[i]);
+    const S q = Term::template energy<S>(rs, rest, prm);
+    out.f = q.v;
+    const T (&gx)[Term::KR] = q.g;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         T g0 = T(0);
@@ -504,7 +494,7 @@ __device__ __forceinline__ void hinge_derivs(const double (&r)[9], const double*
         in.R[c][1] = T(m[c]);
         in.R[c][2] = T(n[c]);
     }
-    frame_gradient<Term, T>(f.v, f.g, r, rest, prm, in.R, out);
+    frame_gradient<Term, T>(r, rest, prm, out);
     const double ru[3] = {l, au, bu};
     T z[3], zz = T(0);
 #pragma unroll
@@ -594,7 +584,7 @@ __device__ __forceinline__ void membrane_derivs(const double (&r)[6], const doub
         in.R[c][1] = T(m[c]);
         in.R[c][2] = T(n[c]);
     }
-    frame_gradient<Term, T>(f.v, f.g, r, rest, prm, in.R, out);
+    frame_gradient<Term, T>(r, rest, prm, out);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -609,13 +599,9 @@ template <class Term, typename T>
 __device__ __forceinline__ void edge_derivs(const double (&r)[3], const double* rest, const double* prm,
                                             ElemOut<Term, T>& out, ClampIn<Term, T, 3>& in) {
     const double rr = dot3(r, r), il = rr > 0.0 ? frsq(rr) : 0.0, l = length_of(rr, il);
-    T R[3][3];   // only the first axis matters: the derivatives across it vanish
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        in.u[c] = rr > 0.0 ? T(r[c] * il) : T(c == 0 ? 1 : 0);
-        R[c][0] = in.u[c];
-        R[c][1] = R[c][2] = T(0);
-    }
+    for (int c = 0; c < 3; ++c) in.u[c] = rr > 0.0 ? T(r[c] * il) : T(c == 0 ? 1 : 0);
+    frame_gradient<Term, T>(r, rest, prm, out);
     T h0, h1;
     if constexpr (Term::NRES > 0) {
         static_assert(Term::NRES == 1, "one residual per edge");
@@ -623,20 +609,14 @@ __device__ __forceinline__ void edge_derivs(const double (&r)[3], const double* 
         const S1 q[3] = {var<S1>(0, l), var<S1>(1, 0.0), var<S1>(2, 0.0)};
         S1 res[1];
         Term::template residual<S1>(q, rest, prm, res);
-        const T rv = T(res[0].v);
-        T g[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) g[c] = rv * res[0].g[c];
         h0 = res[0].g[0] * res[0].g[0];
         h1 = res[0].g[1] * res[0].g[1];
-        frame_gradient<Term, T>(0.5 * res[0].v * res[0].v, g, r, rest, prm, R, out);
     } else {
         using S = HD<3, T>;
         const S q[3] = {var<S>(0, l), var<S>(1, 0.0), var<S>(2, 0.0)};
         const S f = Term::template energy<S>(q, rest, prm);
         h0 = f.h[Packed<3>::at(0, 0)];
         h1 = f.h[Packed<3>::at(1, 1)];
-        frame_gradient<Term, T>(f.v, f.g, r, rest, prm, R, out);
     }
     constexpr double w = wmat(0, 0);
     in.along = T(w * w) * h0;
