@@ -352,8 +352,11 @@ enum { MAD_TUNE_FORCE = 1 };  /* mad_problem_autotune: re-time even if this prob
 
 /* Choose the layout by timing (batched scheduling and the patch-size study, Sec. 7.1): builds each
  * candidate layout (patch scatter with patch targets 128, 256, 512, 1024, each with and without the
- * persistent launch, each with the 4- and (MAD_F32) 8-wave tile; the atomic and the colored scatter), times
- * `reps` evaluations of `mode` on the caller's x_dev and outputs (arguments as for mad_problem_eval;
+ * persistent launch, each with the 4- and (MAD_F32) 8-wave tile; the atomic and the colored scatter; for
+ * problems of edge and vertex terms only, which the patch settings do not change, the present patch layout in
+ * place of the patch candidates), times
+ * `reps` evaluations of `mode` (once for candidates with the same launch) on the caller's x_dev and outputs
+ * (arguments as for mad_problem_eval;
  * their contents are overwritten), and keeps the one with the lowest median time: every candidate
  * writes the same outputs from the same inputs, so the fastest is also the one with the highest
  * algorithmic bytes per second. The choice is cached by a fingerprint of the device, the

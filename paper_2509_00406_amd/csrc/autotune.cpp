@@ -178,10 +178,15 @@ int32_t mad_problem_autotune(mad_problem* p, const double* x, uint32_t mode, dou
     p->profiling = false;
     static const int kFaces[] = {128, 256, 512, 1024};
     std::vector<TuneChoice> cands;
-    for (int w : {4, 8}) {
-        if (w == 8 && p->prec != MAD_F32) continue;
-        for (int f : kFaces)
-            for (int pers = 0; pers < 2; ++pers) cands.push_back({MAD_SCATTER_PATCH, f, pers, w});
+    if (p->light) {
+        // one kernel whatever the patches are (kernels_rows.hip)
+        cands.push_back({MAD_SCATTER_PATCH, p->opt.patch_faces, 0, p->wg_waves});
+    } else {
+        for (int w : {4, 8}) {
+            if (w == 8 && p->prec != MAD_F32) continue;
+            for (int f : kFaces)
+                for (int pers = 0; pers < 2; ++pers) cands.push_back({MAD_SCATTER_PATCH, f, pers, w});
+        }
     }
     cands.push_back({MAD_SCATTER_ATOMIC, 512, 0, 4});
     cands.push_back({MAD_SCATTER_COLOR, 512, 0, 4});
@@ -189,12 +194,15 @@ int32_t mad_problem_autotune(mad_problem* p, const double* x, uint32_t mode, dou
     double best = 1e300;
     TuneChoice bc = {p->scatter, p->opt.patch_faces, p->persistent, p->wg_waves};
     int rc = MAD_OK;
+    double ms = 0.0;
     for (size_t i = 0; rc == MAD_OK && i < cands.size(); ++i) {
         const TuneChoice& c = cands[i];
-        rc = build_layout(p, c.faces, c.scatter, c.persistent, s, c.wg_waves);
-        double ms = 0.0;
-        if (rc == MAD_OK) rc = time_layout(p, x, mode, energy, grad, hess, reps, s, &ms);
-        if (rc != MAD_OK) break;
+        // where the dispatcher hands the patches out, a queue of them is the launch that was just timed
+        if (!(c.persistent == 1 && !p->counter_queue(1, (mode & MAD_HESS) != 0))) {
+            rc = build_layout(p, c.faces, c.scatter, c.persistent, s, c.wg_waves);
+            if (rc == MAD_OK) rc = time_layout(p, x, mode, energy, grad, hess, reps, s, &ms);
+            if (rc != MAD_OK) break;
+        }
         char buf[288];
         std::snprintf(buf, sizeof(buf),
                       "%s{\"scatter\": \"%s\", \"patch_faces\": %d, \"effective_faces\": %d, \"persistent\": %d, "

@@ -63,14 +63,7 @@ static int launch_eval(mad_problem* p, const double* x, uint32_t mode, double* e
         if (hvp) MAD_HIP_TRY(launch_fill(y, m.nv * d, eb, s));
     }
     const int kmode = (hvp || (mode & MAD_HESS)) ? ((mode & MAD_SPD) ? 3 : 2) : ((mode & MAD_GRAD) ? 1 : 0);
-    // Who hands out the patches of a queued (persistent) layout. The Hessian kernels of heavy terms in FP64 hold
-    // a compute unit's registers with one workgroup, so a unit idles between two of them: there a grid of one
-    // workgroup per unit takes patches from a counter (708^2 shell 1.90 ms, one workgroup per patch 1.96).
-    // Elsewhere several workgroups share a unit and the dispatcher is the queue: the counter's round trips to
-    // memory, shared by all units, cost more than they gain (1024^2 shell FP32 1.37 -> 1.33 ms, 700 spheres
-    // 2.76 -> 2.57, 1001^2 symmetric Dirichlet 225 -> 216 us, 200^2 Dirichlet FP64 26 -> 21 us).
-    const bool queue = p->scatter == MAD_SCATTER_PATCH && !rows &&
-                       (p->persistent == 2 || (p->persistent == 1 && p->prec == MAD_F64 && d == 3 && kmode >= 2));
+    const bool queue = p->scatter == MAD_SCATTER_PATCH && !rows && p->counter_queue(p->persistent, kmode >= 2);
     // The patch queue's head and, in the shared static scratch, the FP64 redo queue's words are cleared by a small
     // kernel. A problem's own redo queue is empty between evaluations: the redo pass clears what it used
     // (a launch fewer, 4 us), unless an evaluation ended in an error before it (eval_problem clears it then, so that

@@ -152,6 +152,15 @@ struct mad_problem {
     int32_t* d_row_comp_ptr = nullptr;    // [n_comp + 1] chunks of each component
     int64_t n_row_chunks = 0;
     bool by_rows() const { return light && scatter == MAD_SCATTER_PATCH; }
+    // Who hands out the patches of a queued (persistent) layout. The Hessian kernels of heavy terms in FP64 hold
+    // a compute unit's registers with one workgroup, so a unit idles between two of them: there a grid of one
+    // workgroup per unit takes patches from a counter (708^2 shell 1.90 ms, one workgroup per patch 1.96).
+    // Elsewhere several workgroups share a unit and the dispatcher is the queue: the counter's round trips to
+    // memory, shared by all units, cost more than they gain (1024^2 shell FP32 1.37 -> 1.33 ms, 700 spheres
+    // 2.76 -> 2.57, 1001^2 symmetric Dirichlet 225 -> 216 us, 200^2 Dirichlet FP64 26 -> 21 us).
+    bool counter_queue(int persist, bool hess) const {
+        return persist == 2 || (persist == 1 && prec == MAD_F64 && d == 3 && hess);
+    }
     int32_t* d_tris = nullptr;            // [nt][3] mesh triangles (normals)
     int32_t* d_vf_ptr = nullptr;          // [nv + 1] vertex -> triangles, ascending
     int32_t* d_vf = nullptr;
