@@ -14,12 +14,6 @@ using namespace mad;
 
 namespace {
 
-constexpr int kMaxRows = 512;
-
-// workgroups (partial gradient rows) for a batch: four samples each, at most two workgroups per compute unit of a
-// 256-unit device, which then take further samples in rounds
-int train_rows(int64_t count) { return (int)std::max<int64_t>(1, std::min<int64_t>((count + 3) / 4, kMaxRows)); }
-
 int upload_params(mad_mlp* m, const float* params_host) {
     for (int i = 0; i < kMlpParams; ++i)
         if (!std::isfinite(params_host[i])) return fail(MAD_E_INVALID_ARG, "non-finite network parameter");
@@ -55,7 +49,7 @@ int loss_grad(mad_mlp* m, const float* z, const float* W, const float* dW, const
     for (int i = 0; i < 6; ++i) L.c_g[i] = c_g[i];
     L.lam_g = lam_g;
     L.partial = m->d_partial;
-    L.n_rows = train_rows(count);
+    L.n_rows = train_rows(count, m->max_rows);
     MAD_HIP_TRY(launch_mlp_train(L, s));
     MAD_HIP_TRY(launch_mlp_reduce(m->d_partial, L.n_rows, grad, loss, s));
     return MAD_OK;
@@ -107,7 +101,12 @@ int32_t mad_mlp_create(int32_t hidden, const float* params_host, const float* s_
     alloc((void**)&m->d_grad, sizeof(float) * kMlpParams);
     alloc((void**)&m->d_loss, sizeof(float) * 4);
     alloc((void**)&m->d_step, sizeof(int64_t) * kAdamBlocks);
-    alloc((void**)&m->d_partial, sizeof(float) * (size_t)kMaxRows * (kMlpParams + 1));
+    int n_cu = 0;
+    if (rc == MAD_OK &&
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, m->device) != hipSuccess)
+        rc = fail(MAD_E_HIP, "hipDeviceGetAttribute");
+    m->max_rows = 2 * std::max(n_cu, 1);
+    alloc((void**)&m->d_partial, sizeof(float) * (size_t)m->max_rows * (kMlpParams + 1));
     if (rc == MAD_OK) rc = upload_params(m, params_host);
     if (rc != MAD_OK) {
         free_mlp(m);

@@ -7,6 +7,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "mad.h"
@@ -57,6 +58,11 @@ struct MlpTrainLaunch {
     int n_rows;               // workgroups
 };
 hipError_t launch_mlp_train(const MlpTrainLaunch& L, hipStream_t s);
+// workgroups (partial gradient rows) for a batch: four samples each, at most `most` (two for each compute unit),
+// which then take further samples in rounds
+inline int train_rows(int64_t count, int most) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>((count + 3) / 4, most));
+}
 // sum the per-workgroup partials in a fixed order: grad [kMlpParams], loss [1]
 hipError_t launch_mlp_reduce(const float* partial, int n_rows, float* grad, float* loss, hipStream_t s);
 // Adam on the master copy (its step count, one entry for each of its workgroups, incremented first), then refresh
@@ -79,5 +85,6 @@ struct mad_mlp {
     float* d_grad = nullptr;
     float* d_loss = nullptr;
     int64_t* d_step = nullptr;     // Adam step counts [kAdamBlocks] (device, so a training loop needs no host sync)
-    float* d_partial = nullptr;
+    int max_rows = 0;              // workgroups of a training pass at most
+    float* d_partial = nullptr;    // [max_rows][kMlpParams + 1]
 };

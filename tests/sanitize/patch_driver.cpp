@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "mad_internal.hpp"
+#include "mlp.hpp"
 
 namespace mad {
 // the library's error reporting lives with the C ABI (api.cpp), which this harness does not link
@@ -235,6 +236,13 @@ int main() {
             for (int every : {1, 3}) check_halving(m, target, every);
         for (int64_t wanted : {0, 1, 20, 2048}) check_rows(m, 4, wanted);
     }
+    // training workgroups: one for four samples, at least one, at most what the device has room for
+    for (int most : {2, 64, 512})
+        for (int64_t n : {0ll, 1ll, 4ll, 5ll, 8ll * most, 4000000000ll}) {
+            const int r = train_rows(n, most);
+            CHECK(r >= 1 && r <= most && (r == most || (int64_t)r * 4 >= n));
+            CHECK(r == 1 || (int64_t)(r - 1) * 4 < n);
+        }
     std::printf("patch and row checks passed\n");
     return 0;
 }
