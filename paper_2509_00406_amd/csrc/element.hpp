@@ -160,8 +160,10 @@ __device__ __forceinline__ void hvp_apply(const ElemOut<Term, T>& o, T te, const
 }
 
 // Reciprocal and reciprocal square root: the hardware's in FP32 (about 1 ulp); in FP64 the hardware's
-// estimate and Newton steps, within a few ulps, at a quarter of the instructions of the IEEE division and
-// square root.
+// estimate and Newton steps, at a quarter of the instructions of the IEEE division and square root. Largest error over
+// 4 million values: frcp 0.50 ulp (IEEE 1 / x 0.50), frsq 1.0 (1 / sqrt(x) 1.5), fsqrt 1.7 (sqrt(x) 0.50). fsqrt
+// only sets a rotation's angle; a step that rounds it to 0.5 ulp left the clamped Hessians as they are (1.9e-15 against 64 bits,
+// 101^2 shell) and took 2% more time (708^2 shell 1790 -> 1825 us).
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double frcp(double x) {
     double y = __builtin_amdgcn_rcp(x);
@@ -306,12 +308,11 @@ __device__ __forceinline__ bool jacobi_eig(T (&A)[Packed<N>::N], T (&W)[N][N], T
         // products with their structural zeros and ones fold away at compile time (the element
         // kernels are built without signed zeros and non-finite values)
         jacobi_sweep<N, T>(A, W, dsc, inv);
-        // The test costs about a twentieth of a sweep. A dense 6x6 or 9x9 element Hessian rarely meets
-        // the tolerance within two sweeps (in an FP32 emulation over the benchmark shell: no element
-        // after one, 0.7% of the diamonds after two, never all 64 lanes of a wave), so for those sizes
-        // the test starts after the third; a matrix that would have stopped sooner gets one or two
-        // more sweeps, which only reduce its off-diagonal mass further. Small matrices are tested
-        // after every sweep.
+        // The test costs about a twentieth of a sweep, and the 8x8 of a hinge and the 6x6 of a shell density rarely
+        // meet the tolerance within two sweeps, so for those sizes it starts after the third (FP32, tested from the
+        // first -> from the third: 1024^2 shell 1222 -> 1210 us, 700 spheres 2395 -> 2381, learned density 671 both;
+        // FP64 708^2 shell 1767 -> 1789); a matrix that would have stopped sooner gets one or two more sweeps, which only
+        // reduce its off-diagonal mass further. Small matrices are tested after every sweep.
         constexpr int min_sweeps = N >= 6 ? 3 : 1;
         for (int sweep = 1;; ++sweep) {
             if (sweep >= min_sweeps && jacobi_converged<N, T>(A, dsc, tol)) {

@@ -407,7 +407,6 @@ hipError_t launch_unit_blocks(const int32_t* rowptr, int32_t* unit, int64_t n_en
 hipError_t launch_move_edges(const int32_t* from, int64_t n, const int32_t* map, int32_t* to, int64_t n_to,
                              hipStream_t s);
 
-// sum the halo partials of every shared entry in a fixed order and write it once; zero orphans
 // fixed-order FP64 reduction of the per-patch energies
 struct EnergyArgs {
     const double* partial;            // [n_terms][n_patch]
@@ -419,6 +418,7 @@ struct EnergyArgs {
 hipError_t launch_energy_reduce(const EnergyArgs& E, hipStream_t s);
 hipError_t launch_energy_total(const EnergyArgs& E, hipStream_t s);   // the second pass alone
 
+// sum the halo partials of every shared entry in a fixed order and write it once; zero orphans
 struct GatherLaunch {
     int prec, var_dim, want_grad, want_hess;
     void* grad;
