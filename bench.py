@@ -41,14 +41,14 @@ sys.path.insert(0, ROOT)
 # workload (FP32 + FP64 VALU wave instructions x 64 lanes, FMA = 2), and its HBM traffic per launch
 # (FETCH_SIZE x 2.00 + WRITE_SIZE x 1.00, factors from a 1 GiB copy), from the rocprofv3 counter
 # passes in profiles/k_eval_patch_f32_shell1024_counters.md. Valid for the kernel as profiled there.
-FLOPS_PER_ELEM = {"f32": 8931.8, "f64": None}
+FLOPS_PER_ELEM = {"f32": 9069.1, "f64": None}
 # traffic at the default layout (444-face patches, 4 waves, the dispatcher as the queue)
 TRAFFIC_BYTES = {"f32": 0.9806e9, "f64": None}
 # the same for the 1000^2 cloth step, evaluated by rows (profiles/k_eval_rows_f32_cloth1000_counters.md)
 CLOTH_TRAFFIC_BYTES = {"f32": 0.4545e9, "f64": None}
 # and for the 1001^2 symmetric Dirichlet parameterisation at its default layout (512-face patches;
 # profiles/k_eval_patch_f32_symdir1001_trace_counters.md)
-SYMDIR_TRAFFIC_BYTES = {"f32": 0.3429e9, "f64": None}
+SYMDIR_TRAFFIC_BYTES = {"f32": 0.3430e9, "f64": None}
 
 # MI355X published peaks used as roofline denominators
 HBM_PEAK_GBS = 8000.0
