@@ -287,14 +287,14 @@ int32_t mad_problem_eval(mad_problem *prob, const double *x_dev, uint32_t mode, 
  * fixed memory budget): mad_problem_eval with the same arguments, outputs and errors, that allocates
  * nothing. Every buffer the evaluation writes and reads back within itself (per-patch energies, queue
  * counters, halo partials of entries several patches share, the queue of FP32 elements redone in FP64,
- * vertex normals, network outputs) is taken from a static device array of 64 MiB that each GPU holds
+ * vertex normals, network outputs) is taken from a static device array of 72 MiB that each GPU holds
  * from the library's load until the process ends, instead of from the problem's buffers. The problem
  * must live on the current device (MAD_E_INVALID_ARG otherwise). MAD_E_CAPACITY, before any launch, if
- * the problem needs more than 64 MiB of it (at the default patches the elastic shell of a 724 x 724 vertex
- * grid, 1M triangles, needs 36 MB; the 1024 x 1024 one, 72 MB, does not fit); the FP64 redo queue takes what is left, and an evaluation that queues more elements
- * than that is reported by mad_problem_status as MAD_E_INTERNAL. The array keeps the last call's
- * contents; each call initialises what it reads. Calls on one GPU share its array: calls that overlap
- * on one GPU (other streams, other threads) race and must be ordered by the caller. Per-stage profiling
+ * the problem needs more than 72 MiB of it (at the default patches the elastic shell of a 724 x 724 vertex
+ * grid, 1M triangles, needs 35 MB, the 1024 x 1024 one 70 MB); the FP64 redo queue takes what is left, and an
+ * evaluation that queues more elements than that is reported by mad_problem_status as MAD_E_INTERNAL. The
+ * array keeps the last call's contents; each call initialises what it reads. Calls on one GPU share its array:
+ * calls that overlap on one GPU (other streams, other threads) race and must be ordered by the caller. Per-stage profiling
  * (mad_problem_set_profiling) does not record these calls. Asynchronous on stream. */
 int32_t mad_problem_eval_static(mad_problem *prob, const double *x_dev, uint32_t mode, double *energy_dev,
                                 void *grad_dev, void *hess_dev, void *stream);
