@@ -1,5 +1,5 @@
 """The static scratch holds what it held when patches were grown one after another: an area problem on a 1380^2 grid
-needed 63.1 MiB then; the bisected patches share more entries (67.6 MiB)."""
+fitted 64 MiB then; the bisected patches share more entries (65.4 MiB)."""
 from __future__ import annotations
 
 import numpy as np
